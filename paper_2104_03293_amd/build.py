@@ -21,8 +21,10 @@ ARCH = os.environ.get("SV_OFFLOAD_ARCH", "gfx950")
 LIB = HERE / "libsv.so"
 LIB_SAN = HERE / "libsv_san.so"
 # host code of the C ABI, and the entry point that allocates nothing
-HOST_SRCS = [CSRC / "sv_host_core.cpp", CSRC / "sv_plan.cpp", CSRC / "sv_api.cpp", CSRC / "sv_batch.cpp",
+HOST_SRCS = [CSRC / "sv_host_core.cpp", CSRC / "sv_plan.cpp", CSRC / "sv_tile_host.cpp", CSRC / "sv_api.cpp", CSRC / "sv_batch.cpp",
              CSRC / "sv_noalloc.hip"]
+# gfx950 kernels
+KERNEL_SRCS = [CSRC / "sv_kernels.hip", CSRC / "sv_tile.hip"]
 CLANG_DIR = Path(os.environ.get("SV_CLANG_DIR", "/opt/rocm/llvm/bin"))
 
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -52,7 +54,7 @@ def _compile(src: Path, obj: Path, verbose: bool, extra=()) -> None:
 def build(verbose: bool = False) -> Path:
     objdir = HERE / "_build"
     objdir.mkdir(exist_ok=True)
-    srcs = [CSRC / "sv_kernels.hip", *HOST_SRCS]
+    srcs = [*KERNEL_SRCS, *HOST_SRCS]
     objs = [objdir / (s.stem + ".o") for s in srcs]
     with ThreadPoolExecutor(max_workers=len(srcs)) as ex:
         list(ex.map(lambda so: _compile(so[0], so[1], verbose), zip(srcs, objs)))
@@ -78,9 +80,10 @@ def build_sanitized(verbose: bool = False, out: Path | None = None) -> Path:
     """
     objdir = HERE / "_build"
     objdir.mkdir(exist_ok=True)
-    kobj = objdir / "sv_kernels.o"
-    if not kobj.exists():
-        _compile(CSRC / "sv_kernels.hip", kobj, verbose)
+    kobjs = [objdir / (s.stem + ".o") for s in KERNEL_SRCS]
+    for src, obj in zip(KERNEL_SRCS, kobjs):
+        if not obj.exists():
+            _compile(src, obj, verbose)
     srcs = list(HOST_SRCS)
     objs = [objdir / (s.stem + "_san.o") for s in srcs]
     with ThreadPoolExecutor(max_workers=len(srcs)) as ex:
@@ -90,7 +93,7 @@ def build_sanitized(verbose: bool = False, out: Path | None = None) -> Path:
     tmp = out.with_name(out.name + ".tmp")
     san = ",".join(_SAN)
     cmd = [str(CLANG_DIR / "clang++"), "-shared", "-fPIC", f"-fsanitize={san}", "-shared-libsan", "-o", str(tmp),
-           str(kobj), *map(str, objs), f"-L{rocm / 'lib'}", "-lamdhip64", f"-Wl,-rpath,{rocm / 'lib'}"]
+           *map(str, kobjs), *map(str, objs), f"-L{rocm / 'lib'}", "-lamdhip64", f"-Wl,-rpath,{rocm / 'lib'}"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

@@ -265,6 +265,7 @@ extern "C" int sv_ising_free(sv_ising H) {
     for (void* p : {(void*)H->d_h, (void*)H->d_adj_ptr, (void*)H->d_adj_nbr, (void*)H->d_adj_J, (void*)H->d_ei,
                     (void*)H->d_ej, (void*)H->d_J})
         if (p) (void)hipFree(p);
+    if (H->d_etab) (void)hipFree(H->d_etab);
     for (auto& kv : H->geos) (void)hipFree(kv.second);
     for (auto& kv : H->tfs) (void)hipFree(kv.second);
     delete H;
@@ -289,6 +290,14 @@ static int check_angles(int p, const double* a, const double* b, const char* who
     return SV_OK;
 }
 
+// Phase angles within the range of the small tiles' phase factors (an exponent is at
+// most 4 |gamma| (sum|h| + sum|J|)).
+static bool tile_angles(const sv_ising_s* H, int p, const double* gamma) {
+    double g = 0.0;
+    for (int k = 0; k < p; k++) g = std::max(g, std::fabs(gamma[k]));
+    return 4.0 * g * H->scale <= kTileMaxAngle;
+}
+
 extern "C" int sv_init_plus(sv_state s) {
     if (!s) return fail(SV_ERR_ARG, "sv_init_plus: NULL state");
     Plan plan = make_plan(s->n, s->dt);
@@ -300,7 +309,7 @@ extern "C" int sv_cost_phase(sv_state s, sv_ising H, double gamma) {
     int rc = check_pair(s, H, "sv_cost_phase");
     if (rc) return rc;
     if (!std::isfinite(gamma)) return fail(SV_ERR_NUMERIC, "sv_cost_phase: gamma is not finite");
-    Plan plan = make_plan(s->n, s->dt);
+    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, 1, &gamma));
     Event e{EV_PHASE};
     e.angle = gamma;
     Program prog = build_program({e}, 0, true);
@@ -377,7 +386,7 @@ extern "C" int sv_qaoa_forward(sv_state s, sv_ising H, int p, const double* gamm
     if (rc) return rc;
     rc = check_angles(p, gamma, beta, "sv_qaoa_forward");
     if (rc) return rc;
-    Plan plan = make_plan(s->n, s->dt);
+    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, p, gamma));
     std::vector<Event> ev;
     forward_events(ev, group_order((int)plan.by_nv[1].size(), (int)s->dt, s->n), p, gamma, beta, from_plus != 0, -1);
     Program prog = build_program(ev, 0, knob_for("fuse", (int)s->dt, s->n) != 0);
@@ -407,7 +416,7 @@ int sv_internal_qaoa_energy_fixed(sv_state s, sv_ising H, int p, const double* g
     if (s->device != device)
         return fail(SV_ERR_ARG, "sv_qaoa_energy_noalloc: the state lives on device %d, device %d is current", s->device,
                     device);
-    Plan plan = make_plan(s->n, s->dt);
+    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, p, gamma));
     Program prog = energy_program(s, plan, p, gamma, beta, from_plus);
     return run_program(s, nullptr, H, prog, plan, true, &fx);
 }
@@ -418,7 +427,7 @@ extern "C" int sv_qaoa_energy(sv_state s, sv_ising H, int p, const double* gamma
     if (rc) return rc;
     rc = check_angles(p, gamma, beta, "sv_qaoa_energy");
     if (rc) return rc;
-    Plan plan = make_plan(s->n, s->dt);
+    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, p, gamma));
     Program prog = energy_program(s, plan, p, gamma, beta, from_plus);
     rc = run_program(s, nullptr, H, prog, plan, true);
     if (rc) return rc;
@@ -438,7 +447,7 @@ extern "C" int sv_aqa_run_observe(sv_state s, sv_ising H, int steps, const doubl
     if (rc) return rc;
     const bool want = pgs_per_step || energy_per_step;
     const bool spins = spinz_per_step != nullptr;
-    Plan plan = make_plan(s->n, s->dt);
+    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, steps, gamma));
     std::vector<Event> ev;
     forward_events(ev, group_order((int)plan.by_nv[1].size(), (int)s->dt, s->n), steps, gamma, beta, true,
                    want ? 0 : -1);
@@ -611,7 +620,9 @@ extern "C" int sv_qsds_run(sv_state s, sv_ising H, int steps, double tau, const 
     // layer list and events
     std::vector<double> layers;
     auto add_layer = [&](const double* src) { layers.insert(layers.end(), src, src + (size_t)n * 8); };
-    Plan plan = make_plan(n, s->dt, false, true);
+    std::vector<double> gam((size_t)steps);
+    for (int l = 0; l < steps; l++) gam[l] = tau * B[l];
+    Plan plan = make_plan(n, s->dt, false, true, tile_angles(H, steps, gam.data()));
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)s->dt, n);
     std::vector<Event> ev;
     if (from_plus) ev.push_back(Event{EV_INIT});
@@ -696,6 +707,76 @@ extern "C" int sv_expect(sv_state s, sv_ising H, double* energy, double* p_gs, d
     return SV_OK;
 }
 
+// Result slots of a zeta sweep: [k] E forms, [p + k] mixer forms, [2p ..] norm, <H_C>, P_gs.
+// Events of one reverse sweep after `head`: reductions of psi_p (reduce), zeta, then layer p .. 1
+// undone with the forms.
+static Program zeta_sweep(const std::vector<Event>& head, const std::vector<int>& order, int p, const double* gamma,
+                          const double* beta, double ts, bool reduce, bool fuse) {
+    std::vector<Event> rev = head;
+    if (reduce) {
+        Event r{EV_REDUCE};
+        r.res = 2 * p;
+        rev.push_back(r);
+    }
+    Event z{EV_ZETA};
+    z.angle = ts;
+    rev.push_back(z);
+    for (int k = p - 1; k >= 0; k--) {
+        push_mixer(rev, order, -beta[k], (k % 2) == 0, 1, p + k);
+        Event ef{EV_EFORM};
+        ef.res = k;
+        rev.push_back(ef);
+        if (k > 0) {
+            Event ph{EV_PHASE};
+            ph.angle = -gamma[k];
+            rev.push_back(ph);
+        }
+    }
+    Program prog = build_program(rev, 2 * p + (reduce ? 3 : 0), fuse);
+    prog.passes.back().store = 0;
+    return prog;
+}
+
+// t of zeta = psi +- i t lambda: 1 / (the spread of H_C in |+>).
+static double zeta_scale(const sv_ising_s* H) {
+    double s2 = 0.0;
+    for (double v : H->h) s2 += v * v;
+    for (double v : H->J) s2 += v * v;
+    return s2 > 0.0 ? 1.0 / std::sqrt(s2) : 1.0;
+}
+
+// The adjoint of a state that one tile holds: both zeta sweeps in one launch, a workgroup each,
+// every workgroup running the forward circuit for itself; amplitudes in double precision
+// throughout.  *done = 0 where the state or the program is too large for it.
+static int grad_resident(sv_state_s* psi, sv_ising_s* H, int p, const double* gamma, const double* beta,
+                         int psi_is_forward, double* energy, double* p_gs, double* dgamma, double* dbeta, int* done) {
+    *done = 0;
+    Plan plan = make_plan(psi->n, psi->dt, false, false, tile_angles(H, p, gamma));
+    if (!plan.tile || plan.by_nv[1].size() != 1) return SV_OK;
+    const std::vector<int> order{0};
+    std::vector<Event> head;
+    if (!psi_is_forward) forward_events(head, order, p, gamma, beta, true, -1);
+    const double t = zeta_scale(H);
+    Program prog = zeta_sweep(head, order, p, gamma, beta, t, true, true);
+    int nops = 0;
+    for (const Pass& ps : prog.passes)
+        for (const Op& op : ps.ops) nops += op.kind != 0;
+    if (nops > kMaxTileOps) return SV_OK;
+    *done = 1;
+    int rc = run_tile_program(psi, nullptr, H, prog, plan, true, nullptr, nullptr, true);
+    if (rc) return rc;
+    rc = fetch_results(psi, 2 * prog.nres);
+    if (rc) return rc;
+    const double *plus = psi->w.h_res, *minus = plus + prog.nres;
+    if (energy) *energy = plus[2 * p + 1];
+    if (p_gs) *p_gs = plus[2 * p + 2];
+    for (int k = 0; k < p; k++) {
+        dgamma[k] = (plus[k] - minus[k]) / (2.0 * t);
+        dbeta[k] = (plus[p + k] - minus[p + k]) / (2.0 * t);
+    }
+    return SV_OK;
+}
+
 // Adjoint by two one-vector reverse sweeps.  psi_k and lambda_k = U_{k+1}^+ ... U_p^+ H psi_p
 // are carried back by the same unitaries, so zeta_s = psi + i s t lambda (s = +1, -1) is too,
 // and for a Hermitian A (sum of sigma^x_q, or H_C) expanding the quadratic form gives
@@ -713,13 +794,10 @@ extern "C" int sv_expect(sv_state s, sv_ising H, double* energy, double* p_gs, d
 static int grad_zeta(sv_state_s* psi, sv_state_s* lam, sv_ising_s* H, int p, const double* gamma,
                      const double* beta, int psi_is_forward, double* energy, double* p_gs, double* dgamma,
                      double* dbeta) {
-    Plan plan = make_plan(psi->n, psi->dt);
+    Plan plan = make_plan(psi->n, psi->dt, false, false, tile_angles(H, p, gamma));
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)psi->dt, psi->n);
     const bool fuse = knob_for("fuse", (int)psi->dt, psi->n) != 0;
-    double s2 = 0.0;
-    for (double v : H->h) s2 += v * v;
-    for (double v : H->J) s2 += v * v;
-    const double t = s2 > 0.0 ? 1.0 / std::sqrt(s2) : 1.0;
+    const double t = zeta_scale(H);
     // forward circuit without the last mixer group of layer p
     std::vector<Event> ev;
     Event last{EV_MIX};
@@ -732,35 +810,9 @@ static int grad_zeta(sv_state_s* psi, sv_state_s* lam, sv_ising_s* H, int p, con
         int rc = run_program(psi, nullptr, H, fwd, plan, false);
         if (rc) return rc;
     }
-    // the reverse sweep of one zeta: (last group) reductions, zeta, undo layer p .. 1 with the forms
-    auto sweep = [&](double ts, bool reduce) {
-        std::vector<Event> rev;
-        if (!psi_is_forward) rev.push_back(last);
-        if (reduce) {
-            Event r{EV_REDUCE};
-            r.res = 2 * p;
-            rev.push_back(r);
-        }
-        Event z{EV_ZETA};
-        z.angle = ts;
-        rev.push_back(z);
-        for (int k = p - 1; k >= 0; k--) {
-            push_mixer(rev, order, -beta[k], (k % 2) == 0, 1, p + k);
-            Event ef{EV_EFORM};
-            ef.res = k;
-            rev.push_back(ef);
-            if (k > 0) {
-                Event ph{EV_PHASE};
-                ph.angle = -gamma[k];
-                rev.push_back(ph);
-            }
-        }
-        Program prog = build_program(rev, 2 * p + (reduce ? 3 : 0), fuse);
-        prog.passes.back().store = 0;
-        return prog;
-    };
-    Program plus = sweep(t, true);
-    Program minus = sweep(-t, false);
+    const std::vector<Event> head = psi_is_forward ? std::vector<Event>() : std::vector<Event>{last};
+    Program plus = zeta_sweep(head, order, p, gamma, beta, t, true, fuse);
+    Program minus = zeta_sweep(head, order, p, gamma, beta, -t, false, fuse);
     const hipStream_t lam_stream = lam->stream;
     lam->stream = psi->stream;
     int rc = run_program(lam, nullptr, H, plus, plan, true, nullptr, psi->ptr);
@@ -808,10 +860,15 @@ extern "C" int sv_grad(sv_state psi, sv_state lam, sv_ising H, int p, const doub
     const bool zeta_tiles = psi->dt == SV_C128 ? knob_for("c128t14", dt, nq) == 0
                                                : (knob_for("c64t13", dt, nq) == 0 && knob_for("c64occ", dt, nq) != 0);
     const int zeta = knob_for("adjzeta", dt, nq);
+    if (zeta != 0) {
+        int done = 0;
+        rc = grad_resident(psi, H, p, gamma, beta, psi_is_forward, energy, p_gs, dgamma, dbeta, &done);
+        if (rc || done) return rc;
+    }
     if ((zeta > 0 || (zeta < 0 && psi->dt == SV_C128)) && zeta_tiles)
         return grad_zeta(psi, lam, H, p, gamma, beta, psi_is_forward, energy, p_gs, dgamma, dbeta);
     // both vectors share one tile geometry: plan with the two-vector shape
-    Plan plan = make_plan(psi->n, psi->dt, true);
+    Plan plan = make_plan(psi->n, psi->dt, true, false, tile_angles(H, p, gamma));
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)psi->dt, psi->n);
     std::vector<Event> ev;
     if (!psi_is_forward) forward_events(ev, order, p, gamma, beta, true, -1);

@@ -3,6 +3,7 @@
 // reporting and launch profiling.
 //   sv_host_core.cpp  errors, plan knobs, launch profiling
 //   sv_plan.cpp       tile geometries, pass programs, program execution, ground states
+//   sv_tile_host.cpp  programs on small tiles
 //   sv_api.cpp        states, instances and the circuit entry points
 //   sv_batch.cpp      the batched p = 1 landscape scan
 #pragma once
@@ -11,6 +12,7 @@
 #include <cstdint>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -50,6 +52,7 @@ struct Work {
     double* d_res = nullptr;
     double* h_res = nullptr;
     size_t res_cap = 0;  // doubles
+    bool res_on_host = false;  // the last program wrote its results to h_res itself
     double* d_spin = nullptr;  // per-tile spin partials [ntiles][kTF]
     size_t spin_cap = 0;       // doubles
     double* d_gmat = nullptr;  // general single-qubit layers, kGenBlock doubles per MIX op
@@ -100,6 +103,10 @@ struct sv_ising_s {
     double emin = 0.0;
     uint64_t deg = 0, argmin = 0;
     std::map<GeoKey, GeoBuf*> geos;
+    double* d_etab = nullptr;  // E(z) of every basis state (small tiles, n <= 21)
+    // (dtype, tile bits, group, with a point op) of the small-tile passes run so far: what
+    // calls that may not build tables can rely on
+    std::set<std::tuple<int, int, int, bool>> tile_seen;
     std::map<std::tuple<int, int, int, int, int>, double*> tfs;  // (T, c, lo, g, n) -> per-tile field table
     std::mutex mu;
 };
@@ -155,6 +162,7 @@ struct GenLayers {
 
 // Tile shapes of a program: [1] one-vector, [2] two-vector.
 struct Plan {
+    bool tile = false;  // small tiles (run_tile_program); both shapes are then the same
     std::vector<Geometry> by_nv[3];  // [1]: one-vector tile shape, [2]: two-vector shape
 };
 
@@ -165,12 +173,25 @@ int device_cu_count(int dev);  // compute units of a device (cached; 256 on MI35
 
 // ---------------------------------------------------------------- planning and execution
 std::vector<Geometry> plan_groups(int n, sv_dtype dt, int nv, bool grad = false, bool general = false);
-Plan make_plan(int n, sv_dtype dt, bool grad = false, bool general = false);
+// tile_ok: the program may run on the small tiles (tile_bits), if its size takes them.
+Plan make_plan(int n, sv_dtype dt, bool grad = false, bool general = false, bool tile_ok = true);
+int tile_bits(int n, sv_dtype dt);
+std::vector<Geometry> tile_groups(int n, int T);
 Program build_program(const std::vector<Event>& evs, int nres, bool fuse);
 // fx != nullptr: the call may not allocate (see run_program in sv_plan.cpp).
 int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, const Plan& plan, bool need_ground,
                 const FixedScratch* fx = nullptr, const void* first_src = nullptr);
+// run_program on small tiles.  dual (one-tile states): two workgroups run the program with
+// PT_ZETA's t and -t and store no state; the second's results follow the first's.
+int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, const Plan& plan, bool need_ground,
+                     const FixedScratch* fx = nullptr, const void* first_src = nullptr, bool dual = false);
 int fetch_results(sv_state_s* s, int nres);
+int ensure_work(sv_state_s* s, size_t part_doubles, size_t res_doubles);
+// Pinned staging buffer for nblk matrix blocks of general layers (waits until an earlier
+// copy has left it), and the copy to the device.
+int stage_matrices(sv_state_s* s, size_t nblk, double** host);
+int send_matrices(sv_state_s* s, size_t nblk);
+IsingDev ising_dev(const sv_ising_s* H);
 // Frees the instance-free geometry tables (mixer-only programs); called when the
 // last state is freed, so they live no longer than the states that use them.
 void release_plain_geos();

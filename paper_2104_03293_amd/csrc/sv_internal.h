@@ -232,6 +232,60 @@ struct StreamArgs {
 int launch_stream(int dtype, void* p, const StreamArgs& a, void* stream);
 int launch_ground_finish(const GroundArgs& a, double* out_e, uint64_t* out_cnt,
                          uint64_t* out_arg, void* stream);
+// ---------------------------------------------------------------- small tiles
+// Tile programs of states that the large tiles cannot spread over the chip
+// (sv_tile.hip).  Layout j of a tile holds tile bits [lb, lb + 4) in registers,
+// lb = (lbpack >> 8j) & 255.  Reduction columns: part[column][tile].
+constexpr int kTileR = 4;
+constexpr int kMaxTileOps = 104;
+constexpr double kTileMaxAngle = 65536.0;  // phase angles gamma * E beyond it use the large tiles
+struct TileOp {
+    uint32_t w0;   // OpKind | MixFlags / PointFlags << 8
+    int16_t part;  // MIX_GBETA, PT_REDUCE: first column
+    int16_t part2; // PT_GGAMMA, PT_EFORM: column
+    int32_t aux;   // MIX_GEN: matrix block; PT_SPINZ: first column
+    int32_t pad;
+    double a, b;   // as Op::a, Op::b
+};
+struct TileArgs {
+    void* psi;
+    void* lam;
+    const void* src;        // psi is loaded from here when non-null
+    double* part;
+    const double* E;        // energy table of the instance, E(z) for every basis state
+    const double* gmat;
+    uint64_t ntiles;
+    int32_t n, c, lo, g;
+    uint32_t phantom;
+    int32_t nlayouts;
+    uint32_t lbpack;
+    uint32_t act_fwd, act_bwd;  // active register slots of layout j: bits 8j .. 8j + 3
+    int32_t load, store;    // as PassArgs
+    int32_t need_e;         // bit 0: a point op runs in layout 0, bit 1: in the last layout
+    int32_t nops;
+    int32_t swz;
+    int32_t spin_cols;      // columns of a PT_SPINZ op (T + 1, or n where one tile holds the state)
+    int32_t dual;           // two workgroups run the program with PT_ZETA's t and -t, the second
+    int32_t dual_cols;      //   writing its columns dual_cols further on
+    int32_t resident;       // the program runs in one launch of one workgroup
+    int32_t feat;           // kernel variant: 0 plain, 1 adjoint forms, 2 general layers and spin sums
+    double emin, etol, amp0;
+    double Q[2][1 << kTileR];  // layout 0 and the last: sum of 4 J over the register-bit pairs set in r
+    TileOp ops[kMaxTileOps];
+};
+static_assert(sizeof(TileArgs) <= 4096, "kernel arguments");
+struct GatherArgs {
+    const double* part;
+    double* out;
+    uint32_t ntiles;
+    uint16_t first[257];    // result i sums seg[first[i]] .. seg[first[i + 1] - 1]
+    uint32_t seg[768];      // column | (sign bit of the tile index, 255: none) << 24
+};
+static_assert(sizeof(GatherArgs) <= 4096, "kernel arguments");
+int launch_energy_table(const IsingDev& is, double* E, void* stream);
+int launch_tile(int dtype, int nv, int T, const TileArgs& a, void* stream);
+int launch_gather(const GatherArgs& a, int n, void* stream);
+
 // ---------------------------------------------------------------- batch scan
 // One instance of the p = 1 landscape scan (device array of these).
 struct BatchInst {

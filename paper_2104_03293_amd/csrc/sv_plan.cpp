@@ -242,6 +242,20 @@ std::vector<Geometry> plan_groups(int n, sv_dtype dt, int nv, bool grad, bool ge
     return out;
 }
 
+// Groups of a small-tile plan: two at most (n <= 2 T - 3), no lane butterflies, whole-tile
+// exchanges (all four register slots free).
+std::vector<Geometry> tile_groups(int n, int T) {
+    std::vector<Geometry> out;
+    if (n <= T) {
+        out.push_back(make_geometry(n, T, kTileR, n, n, 0, 3, 0u, false));
+    } else {
+        out.push_back(make_geometry(n, T, kTileR, T, T, 0, 3, 0u, false));
+        const int g = n - T;
+        out.push_back(make_geometry(n, T, kTileR, T - g, T, g, 3, 0u, false));
+    }
+    return out;
+}
+
 static int global_bit(const Geometry& geo, int l) {
     if (l >= geo.n) return -1;
     if (l < geo.c) return l;
@@ -688,7 +702,7 @@ static void finalize_program(Program& prog, const std::vector<Geometry>* groups_
 }
 
 // ============================================================================ execution
-static int ensure_work(sv_state_s* s, size_t part_doubles, size_t res_doubles) {
+int ensure_work(sv_state_s* s, size_t part_doubles, size_t res_doubles) {
     Work& w = s->w;
     if (part_doubles > w.part_cap) {
         if (w.d_part) (void)hipFree(w.d_part);
@@ -710,7 +724,7 @@ static int ensure_work(sv_state_s* s, size_t part_doubles, size_t res_doubles) {
     return SV_OK;
 }
 
-static IsingDev ising_dev(const sv_ising_s* H) {
+IsingDev ising_dev(const sv_ising_s* H) {
     IsingDev d{};
     if (!H) return d;
     d.h = H->d_h;
@@ -764,14 +778,49 @@ static int get_tf(sv_ising_s* H, const Geometry& geo, const GeoBuf* gb, hipStrea
     return SV_OK;
 }
 
+int stage_matrices(sv_state_s* s, size_t nblk, double** host) {
+    const size_t need = nblk * (size_t)kGenBlock;
+    // the staging buffer may still feed the previous call's copy
+    HIPCHECK(hipStreamSynchronize(s->stream));
+    if (need > s->w.gmat_cap) {
+        if (s->w.d_gmat) (void)hipFree(s->w.d_gmat);
+        if (s->w.h_gmat) (void)hipHostFree(s->w.h_gmat);
+        s->w.d_gmat = nullptr;
+        s->w.h_gmat = nullptr;
+        s->w.gmat_cap = 0;
+        HIPCHECK(hipMalloc(&s->w.d_gmat, need * sizeof(double)));
+        HIPCHECK(hipHostMalloc(&s->w.h_gmat, need * sizeof(double), hipHostMallocDefault));
+        s->w.gmat_cap = need;
+    }
+    *host = s->w.h_gmat;
+    return SV_OK;
+}
+
+int send_matrices(sv_state_s* s, size_t nblk) {
+    const hipError_t e = hipMemcpyAsync(s->w.d_gmat, s->w.h_gmat, nblk * (size_t)kGenBlock * sizeof(double),
+                                        hipMemcpyHostToDevice, s->stream);
+    if (e != hipSuccess) {
+        s->failed = true;
+        return fail(SV_ERR_HIP, "hipMemcpyAsync (layer matrices): %s", hipGetErrorString(e));
+    }
+    return SV_OK;
+}
+
 // Energies on a grid Z / q are computed exactly in FP64, so the ground set compares exactly.
 double ground_tol(const sv_ising_s* H) { return H->qden > 0 ? 0.0 : 1e-9 * std::max(1.0, H->scale); }
 
 
 
 // grad: the adjoint family, whose one- and two-vector tiles share T.
-Plan make_plan(int n, sv_dtype dt, bool grad, bool general) {
+Plan make_plan(int n, sv_dtype dt, bool grad, bool general, bool tile_ok) {
     Plan pl;
+    // small tiles (complex128 two-vector programs, chosen by knob adjzeta only, have no kernels there)
+    const int tb = tile_ok && !(grad && dt == SV_C128) ? tile_bits(n, dt) : 0;
+    if (tb > 0) {
+        pl.tile = true;
+        pl.by_nv[1] = pl.by_nv[2] = tile_groups(n, tb);
+        return pl;
+    }
     // complex64 one-vector programs may use the 13-bit tiles of the adjoint family
     // (not programs with general single-qubit layers, whose kernels exist for 14-bit tiles)
     if (dt == SV_C64 && !general && knob_for("c64t13", (int)dt, n) != 0) grad = true;
@@ -787,6 +836,8 @@ Plan make_plan(int n, sv_dtype dt, bool grad, bool general) {
 // first_src: the first pass loads psi from this buffer instead of s (out of place).
 int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, const Plan& plan,
                        bool need_ground, const FixedScratch* fx, const void* first_src) {
+    if (plan.tile) return run_tile_program(s, lam, H, prog, plan, need_ground, fx, first_src);
+    s->w.res_on_host = false;
     finalize_program(prog, plan.by_nv);
     if (s->failed) return fail(SV_ERR_HIP, "state is in a failed state after an earlier HIP error");
     double emin = 0.0, etol = 0.0;
@@ -928,24 +979,14 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
         }
         const GenLayers gl = unit_diagonal_layers(prog.layers, nl, s->n, knob_for("genunit", (int)s->dt, s->n) != 0,
                                                   pass_ops);
-        const size_t need = nblk * (size_t)kGenBlock;
-        // the staging buffer may still feed the previous call's copy
-        HIPCHECK(hipStreamSynchronize(s->stream));
-        if (need > s->w.gmat_cap) {
-            if (s->w.d_gmat) (void)hipFree(s->w.d_gmat);
-            if (s->w.h_gmat) (void)hipHostFree(s->w.h_gmat);
-            s->w.d_gmat = nullptr;
-            s->w.h_gmat = nullptr;
-            s->w.gmat_cap = 0;
-            HIPCHECK(hipMalloc(&s->w.d_gmat, need * sizeof(double)));
-            HIPCHECK(hipHostMalloc(&s->w.h_gmat, need * sizeof(double), hipHostMallocDefault));
-            s->w.gmat_cap = need;
-        }
+        double* h_gmat = nullptr;
+        rc = stage_matrices(s, nblk, &h_gmat);
+        if (rc) return rc;
         for (size_t pi = 0; pi < prog.passes.size(); pi++) {
             const Geometry& geo = plan.by_nv[prog.passes[pi].nv][prog.passes[pi].group];
             for (int i = 0; i < kMaxOps; i++) {
                 if (genblk[pi][i] < 0) continue;
-                double* blk = s->w.h_gmat + (size_t)genblk[pi][i] * kGenBlock;
+                double* blk = h_gmat + (size_t)genblk[pi][i] * kGenBlock;
                 Op& op = prog.passes[pi].ops[i];
                 const int layer = op.qidx;
                 bool real = true;
@@ -970,12 +1011,8 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
                 }
             }
         }
-        hipError_t e = hipMemcpyAsync(s->w.d_gmat, s->w.h_gmat, need * sizeof(double), hipMemcpyHostToDevice,
-                                      s->stream);
-        if (e != hipSuccess) {
-            s->failed = true;
-            return fail(SV_ERR_HIP, "hipMemcpyAsync (layer matrices): %s", hipGetErrorString(e));
-        }
+        rc = send_matrices(s, nblk);
+        if (rc) return rc;
     }
     const int ntmin = knob_for("ntmin", (int)s->dt, s->n);
     const int persist = knob_for("persist", (int)s->dt, s->n);
@@ -1111,7 +1148,9 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
 
 int fetch_results(sv_state_s* s, int nres) {
     if (nres <= 0) return SV_OK;
-    hipError_t e = hipMemcpyAsync(s->w.h_res, s->w.d_res, nres * sizeof(double), hipMemcpyDeviceToHost, s->stream);
+    hipError_t e = hipSuccess;
+    if (!s->w.res_on_host)
+        e = hipMemcpyAsync(s->w.h_res, s->w.d_res, nres * sizeof(double), hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) {
         s->failed = true;

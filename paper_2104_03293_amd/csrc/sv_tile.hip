@@ -1,0 +1,546 @@
+// gfx950 kernels for states that do not fill the chip with the large tiles of
+// sv_kernels.hip: compact tile programs on 2^10 .. 2^13 amplitudes per
+// workgroup, the per-instance energy table they read, and the second stage of
+// their reductions.
+//
+// What bounds such a pass is latency, not bandwidth (the state sits in L2 or
+// the last-level cache): kernel start, table reads, the serial chain of
+// butterflies and exchanges of one workgroup, and instruction fetch, since
+// every workgroup runs its code once.  So the tiles are small enough to reach
+// every CU, all the layout arithmetic is done in registers instead of read
+// from tables, the energy comes from a table of E(z) (R + 1 reads per thread),
+// phase factors are computed in place instead of by a launch of their own, and
+// the code is a loop over ops and layouts (one copy of each op's code).
+// Measured against the large tiles: n = 12 complex64, p = 4 (one launch) 93 ->
+// 24 us per evaluation, n = 18 complex128, p = 8 184 -> 117 us (passes of 15-22
+// us -> 12-14 us), n = 21 real couplings, p = 3 171 -> 95 us.
+#include <hip/hip_runtime.h>
+
+#include "sv_device.h"
+#include "sv_internal.h"
+
+namespace svk {
+
+// (cos x, -sin x) for |x| <= kTileMaxAngle (the host sends programs with larger
+// phase angles to the large tiles).  Two-term reduction by pi/2 with fused
+// multiply-adds (x - k hi(pi/2) is exact for |x| <= 2^16: both are multiples of
+// 2^-52 and the difference is below 1) and Taylor polynomials on [-pi/4, pi/4]
+// (first dropped terms: 8e-20 for the sine, 2e-18 for the cosine).
+__device__ __forceinline__ double2 cis_neg(double x) {
+    const double k = rint(x * 0.63661977236758134);
+    const double r = fma(-k, 6.123233995736766e-17, fma(-k, 1.5707963267948966, x));
+    const double z = r * r;
+    double s = 1.0 / 355687428096000.0, c = 1.0 / 20922789888000.0;
+    s = fma(s, z, -1.0 / 1307674368000.0);
+    c = fma(c, z, -1.0 / 87178291200.0);
+    s = fma(s, z, 1.0 / 6227020800.0);
+    c = fma(c, z, 1.0 / 479001600.0);
+    s = fma(s, z, -1.0 / 39916800.0);
+    c = fma(c, z, -1.0 / 3628800.0);
+    s = fma(s, z, 1.0 / 362880.0);
+    c = fma(c, z, 1.0 / 40320.0);
+    s = fma(s, z, -1.0 / 5040.0);
+    c = fma(c, z, -1.0 / 720.0);
+    s = fma(s, z, 1.0 / 120.0);
+    c = fma(c, z, 1.0 / 24.0);
+    s = fma(s, z, -1.0 / 6.0);
+    s = fma(s * z, r, r);
+    const double h = 0.5 * z, w = 1.0 - h;  // 1 - z/2 + z^2 c with the rounding error of 1 - z/2 put back
+    c = w + fma(z * z, c, (1.0 - w) - h);
+    const int q = (int)k;
+    const double cs = (q & 1) ? s : c, sn = (q & 1) ? c : s;
+    return make_double2(((q + 1) & 2) ? -cs : cs, (q & 2) ? sn : -sn);
+}
+
+// E(z) of every basis state (Eq. HC), one thread per state: a compensated sum,
+// so that the table holds E(z) rounded once whatever the number of terms.
+__global__ void __launch_bounds__(256) k_energy_table(const IsingDev is, double* __restrict__ E, uint64_t N) {
+    const uint64_t z = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    double s = 0.0, e = 0.0;
+    auto add = [&](double x) {
+        const double t = s + x, b = t - s;
+        e += (s - (t - b)) + (x - b);
+        s = t;
+    };
+    for (int i = 0; i < is.n; i++) add(((z >> i) & 1) ? is.h[i] : -is.h[i]);
+    for (int k = 0; k < is.m; k++) {
+        const uint64_t same = ~((z >> is.ei[k]) ^ (z >> is.ej[k])) & 1ull;
+        add(same ? is.J[k] : -is.J[k]);
+    }
+    if (z < N) E[z] = s + e;
+}
+
+int launch_energy_table(const IsingDev& is, double* E, void* stream) {
+    const uint64_t N = 1ull << is.n;
+    hipLaunchKernelGGL(k_energy_table, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, (hipStream_t)stream, is, E, N);
+    return (int)hipGetLastError();
+}
+
+// Products with the fused operations spelt out, so that every variant of the
+// kernel rounds alike.
+template <typename X>
+__device__ __forceinline__ X mul_re(X ar, X ai, X br, X bi) {
+    return fma(ar, br, -(ai * bi));
+}
+template <typename X>
+__device__ __forceinline__ X mul_im(X ar, X ai, X br, X bi) {
+    return fma(ar, bi, ai * br);
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
+// Workgroup sums of N per-thread values in a fixed order, handed to
+// put(i, sum) by thread i (any thread for one wave).
+template <int N, int NW, typename Put>
+__device__ __forceinline__ void block_sums(double (&v)[N], double (*s_red)[kTF], Put put) {
+    static_assert(N <= kTF, "reduction row");
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < N; i++) v[i] = wave_sum(v[i]);
+    if constexpr (NW == 1) {
+        if (t == 0)
+#pragma unroll
+            for (int i = 0; i < N; i++) put(i, v[i]);
+    } else {
+        if ((t & 63) == 0)
+#pragma unroll
+            for (int i = 0; i < N; i++) s_red[t >> 6][i] = v[i];
+        __syncthreads();
+        if (t < N) {
+            double x = 0.0;
+            for (int w = 0; w < NW; w++) x += s_red[w][t];
+            put(t, x);
+        }
+        __syncthreads();
+    }
+}
+
+// One tile program.  Real: stored amplitudes; Acc: amplitudes in registers and
+// LDS; 2^T amplitudes per workgroup, 2^R per thread and vector, NV vectors.
+// Layout j holds tile bits [lb[j], lb[j] + R) in registers and the others in
+// the thread index, in order.  FEAT: 0 uniform mixers, phases and the energy
+// reduction; 1 also the forms of the adjoint sweeps; 2 also general layers and
+// spin sums (each left out where it is not needed: registers and code size).
+template <typename Real, typename Acc, int T, int R, int NV, int FEAT>
+__global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
+    using V2 = typename V2T<Real>::type;
+    using A2 = typename V2T<Acc>::type;
+    constexpr int NT = 1 << (T - R);
+    constexpr int NR = 1 << R;
+    constexpr int NW = NT / 64;
+    static_assert(NT >= 64 && R == 4, "whole waves, 16 amplitudes per thread");
+    __shared__ A2 xbuf[1 << T];
+    __shared__ double s_red[NW][kTF];
+
+    const uint32_t t = threadIdx.x;
+    // the op list is read where it lies (a dynamic index into a by-value
+    // argument would copy it to scratch memory)
+    const SV_CONST TileArgs* ka = (const SV_CONST TileArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    const uint64_t tile = a.dual ? 0 : blockIdx.x;
+    const bool second = a.dual && blockIdx.x != 0;
+    const TileGeom tg{a.c, a.lo, a.g};
+    const uint64_t base = tg.base(tile);
+    const int K = a.nlayouts;
+    const uint32_t ph = a.phantom;
+    double* const part = a.part + (second ? (uint64_t)a.dual_cols * a.ntiles : 0ull);
+
+    auto lbase = [&](int j) { return (a.lbpack >> (8 * j)) & 255; };
+    auto tpart = [&](int b) { return (t & ((1u << b) - 1u)) | ((t >> b) << (b + R)); };
+    int cur = 0;
+    int ab = lbase(0);
+    uint32_t thr = tpart(ab);
+
+    // ---- load in layout 0
+    Acc vr[NV][NR], vi[NV][NR];
+    {
+        const uint64_t off = base | tg.gmap(thr & ~ph);
+#pragma unroll
+        for (int v = 0; v < NV; v++) {
+            const V2* __restrict__ src =
+                reinterpret_cast<const V2*>(v == 1 ? a.lam : (a.src ? a.src : a.psi)) + off;
+            const bool ld = (a.load >> v) & 1;
+#pragma unroll
+            for (int r = 0; r < NR; r++) {
+                const uint32_t ur = (uint32_t)r << ab;
+                Acc xr = 0, xi = 0;
+                if (((thr | ur) & ph) == 0u) {
+                    if (ld) {
+                        const V2 x = src[tg.gmap(ur)];
+                        xr = x.x;
+                        xi = x.y;
+                    } else if (v == 0 && (a.load & 4)) {
+                        xr = (Acc)a.amp0;
+                    }
+                }
+                vr[v][r] = xr;
+                vi[v][r] = xi;
+            }
+        }
+    }
+    // energies of the thread's register 0 and of the registers one bit away from
+    // it, for the layouts that hold a point op: E(r) = E(0) + sum_k r_k d_k + Q(r)
+    double ev[2][R + 1];
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+#pragma unroll
+        for (int k = 0; k <= R; k++) ev[s][k] = 0.0;
+        if ((a.need_e >> s) & 1) {
+            const int b = lbase(s ? K - 1 : 0);
+            const uint32_t u = tpart(b) & ~ph;
+            const double* __restrict__ E = a.E + base;
+            ev[s][0] = E[tg.gmap(u)];
+#pragma unroll
+            for (int k = 0; k < R; k++) ev[s][1 + k] = E[tg.gmap((u | (1u << (b + k))) & ~ph)];
+        }
+    }
+
+    double pend[NV];  // uniform scale every register of vector v still has to be multiplied by
+#pragma unroll
+    for (int v = 0; v < NV; v++) pend[v] = 1.0;
+
+#pragma unroll 1
+    for (int oi = 0; oi < a.nops; oi++) {
+        const uint32_t w0 = ka->ops[oi].w0;
+        const int kind = (int)(w0 & 255u), fl = (int)(w0 >> 8);
+        const double opa = ka->ops[oi].a, opb = ka->ops[oi].b;
+        const int part0 = ka->ops[oi].part, part2 = ka->ops[oi].part2, aux = ka->ops[oi].aux;
+        auto put_at = [&](int col) {
+            return [&, col](int i, double x) { part[(uint64_t)(col + i) * a.ntiles + tile] = x; };
+        };
+        if (kind == OP_MIX) {
+            const bool fwd = cur == 0;
+            double gsum = 0.0;
+            const Acc tq = (Acc)opa;
+#pragma unroll 1
+            for (int step = 0; step < K; step++) {
+                const int j = fwd ? step : K - 1 - step;
+                if (step > 0) {
+                    // LDS exchange into layout j.  A thread writes only the slots it read
+                    // last, so one barrier (between writes and reads) is enough.
+                    const int nb = lbase(j);
+                    const uint32_t nthr = tpart(nb);
+                    constexpr uint32_t SZ = (uint32_t)sizeof(A2);
+                    uint32_t bs[R], bd[R];
+#pragma unroll
+                    for (int k = 0; k < R; k++) {
+                        bs[k] = lds_swizzle(1u << (ab + k), a.swz) * SZ;
+                        bd[k] = lds_swizzle(1u << (nb + k), a.swz) * SZ;
+                    }
+                    const uint32_t s0 = lds_swizzle(thr, a.swz) * SZ, d0 = lds_swizzle(nthr, a.swz) * SZ;
+                    char* xb = reinterpret_cast<char*>(xbuf);
+#pragma unroll
+                    for (int v = 0; v < NV; v++) {
+                        if (v > 0) __syncthreads();  // the first vector's reads
+                        uint32_t ad = s0;
+#pragma unroll
+                        for (int i = 0; i < NR; i++) {
+                            if (i > 0) ad ^= bs[__builtin_ctz(i)];
+                            const int r = i ^ (i >> 1);
+                            A2 x;
+                            x.x = vr[v][r];
+                            x.y = vi[v][r];
+                            *reinterpret_cast<A2*>(xb + ad) = x;
+                        }
+                        __syncthreads();
+                        ad = d0;
+#pragma unroll
+                        for (int i = 0; i < NR; i++) {
+                            if (i > 0) ad ^= bd[__builtin_ctz(i)];
+                            const int r = i ^ (i >> 1);
+                            const A2 x = *reinterpret_cast<const A2*>(xb + ad);
+                            vr[v][r] = x.x;
+                            vi[v][r] = x.y;
+                        }
+                    }
+                    cur = j;
+                    ab = nb;
+                    thr = nthr;
+                }
+                const int act = (int)(((fwd ? a.act_fwd : a.act_bwd) >> (8 * j)) & 255u);
+                if (FEAT == 2 && (fl & MIX_GEN)) {
+                    // general single-qubit layer: (u, v) <- (m00 u + m01 v, m10 u + m11 v)
+                    const SV_CONST double* M = (const SV_CONST double*)(a.gmat + (uint64_t)aux * kGenBlock);
+#pragma unroll
+                    for (int k = 0; k < R; k++) {
+                        if (!((act >> k) & 1)) continue;
+                        const SV_CONST double* m = M + 8 * (ab + k);
+                        const Acc a0 = (Acc)m[0], a1 = (Acc)m[1], b0 = (Acc)m[2], b1 = (Acc)m[3];
+                        const Acc c0 = (Acc)m[4], c1 = (Acc)m[5], d0 = (Acc)m[6], d1 = (Acc)m[7];
+#pragma unroll
+                        for (int r = 0; r < NR; r++) {
+                            if (r & (1 << k)) continue;
+                            const int r2 = r | (1 << k);
+                            const Acc ur = vr[0][r], ui = vi[0][r], wr = vr[0][r2], wi = vi[0][r2];
+                            vr[0][r] = fma(a0, ur, fma(-a1, ui, fma(b0, wr, -b1 * wi)));
+                            vi[0][r] = fma(a0, ui, fma(a1, ur, fma(b0, wi, b1 * wr)));
+                            vr[0][r2] = fma(c0, ur, fma(-c1, ui, fma(d0, wr, -d1 * wi)));
+                            vi[0][r2] = fma(c0, ui, fma(c1, ur, fma(d0, wi, d1 * wr)));
+                        }
+                    }
+                    continue;
+                }
+#pragma unroll
+                for (int k = 0; k < R; k++) {
+                    if (!((act >> k) & 1)) continue;
+                    if (NV == 2 && FEAT == 1 && (fl & MIX_GBETA)) {
+                        // Im(conj(lam_a) psi_b) + Im(conj(lam_b) psi_a), summed in FP64
+                        double gb = 0.0;
+#pragma unroll
+                        for (int r = 0; r < NR; r++) {
+                            if (r & (1 << k)) continue;
+                            const int r2 = r | (1 << k);
+                            const Acc q = vr[NV - 1][r] * vi[0][r2] - vi[NV - 1][r] * vr[0][r2] +
+                                          vr[NV - 1][r2] * vi[0][r] - vi[NV - 1][r2] * vr[0][r];
+                            gb += (double)q;
+                        }
+                        gsum += gb * pend[0] * pend[NV - 1];
+                    }
+#pragma unroll
+                    for (int v = 0; v < NV; v++) {
+                        if (NV == 2 && !(fl & (1 << v))) continue;
+#pragma unroll
+                        for (int r = 0; r < NR; r++) {
+                            if (r & (1 << k)) continue;
+                            const int r2 = r | (1 << k);
+                            butterfly<Acc>(vr[v][r], vi[v][r], vr[v][r2], vi[v][r2], tq);
+                        }
+                        pend[v] *= opb;
+                    }
+                }
+                if (FEAT == 1 && NV == 1 && (fl & MIX_GBETA)) {
+                    // quadratic forms 2 Re(conj(a) b) of the pairs of every active slot, from the
+                    // values after the round (a butterfly leaves the form of every qubit unchanged)
+                    double g2[2] = {0.0, 0.0};
+#pragma unroll
+                    for (int k = 0; k < R; k++) {
+                        if (!((act >> k) & 1)) continue;
+#pragma unroll
+                        for (int r = 0; r < NR; r++) {
+                            if (r & (1 << k)) continue;
+                            const int r2 = r | (1 << k);
+                            g2[k & 1] = fma((double)vr[0][r], (double)vr[0][r2], g2[k & 1]);
+                            g2[k & 1] = fma((double)vi[0][r], (double)vi[0][r2], g2[k & 1]);
+                        }
+                    }
+                    gsum += 2.0 * (g2[0] + g2[1]) * pend[0] * pend[0];
+                }
+            }
+            if (FEAT == 1 && (fl & MIX_GBETA)) {
+                double gv[1] = {gsum};
+                block_sums<1, NW>(gv, s_red, put_at(part0));
+            }
+            continue;
+        }
+        // ---- OP_POINT in the current layout (0 or K - 1)
+        const int es = cur == 0 ? 0 : 1;
+        double e0 = es ? ev[1][0] : ev[0][0], d[R];
+#pragma unroll
+        for (int k = 0; k < R; k++) d[k] = (es ? ev[1][1 + k] : ev[0][1 + k]) - e0;
+        // per-register loop in Gray-code order (E changes by +-d[k]), f(r, E(r))
+        auto each = [&](auto f) {
+            double e_run = e0;
+#pragma unroll
+            for (int i = 0; i < NR; i++) {
+                const int r = i ^ (i >> 1);
+                if (i > 0) {
+                    const int k = __builtin_ctz(i);
+                    e_run += ((r >> k) & 1) ? d[k] : -d[k];
+                }
+                f(r, e_run + ka->Q[es][r]);
+            }
+        };
+        if (fl & (PT_REDUCE | PT_SPINZ)) {
+            double rv[3] = {0.0, 0.0, 0.0};
+            double Sk[R];
+#pragma unroll
+            for (int k = 0; k < R; k++) Sk[k] = 0.0;
+            each([&](int r, double e) {
+                const double pr = (double)vr[0][r], pi = (double)vi[0][r];
+                const double p2 = fma(pr, pr, pi * pi);
+                rv[0] += p2;
+                rv[1] = fma(e, p2, rv[1]);
+                if (fabs(e - a.emin) <= a.etol) rv[2] += p2;
+                if constexpr (FEAT == 2)
+#pragma unroll
+                    for (int k = 0; k < R; k++) Sk[k] += ((r >> k) & 1) ? p2 : -p2;
+            });
+            const double s2 = pend[0] * pend[0];
+            const double nrm = rv[0] * s2;
+            if (FEAT == 2 && (fl & PT_SPINZ)) {
+                // entry l < T: sum of |psi|^2 s_l over the tile, entry T: sum of |psi|^2
+                // (tile bit l is register bit l - ab or thread bit l or l - R)
+                double sv[T + 1];
+#pragma unroll
+                for (int l = 0; l < T; l++) {
+                    const int k = l - ab;
+                    const int j = l < ab ? l : l - R;
+                    double x = ((t >> (j & 31)) & 1u) ? nrm : -nrm;
+#pragma unroll
+                    for (int q = 0; q < R; q++)
+                        if (k == q) x = Sk[q] * s2;
+                    sv[l] = x;
+                }
+                sv[T] = nrm;
+                const int ncol = a.spin_cols;
+                block_sums<T + 1, NW>(sv, s_red, [&](int i, double x) {
+                    if (i < ncol) part[(uint64_t)(aux + i) * a.ntiles + tile] = x;
+                });
+            }
+            if (fl & PT_REDUCE) {
+#pragma unroll
+                for (int i = 0; i < 3; i++) rv[i] *= s2;
+                block_sums<3, NW>(rv, s_red, put_at(part0));
+            }
+        }
+        if constexpr (NV == 2) {
+            if (fl & PT_LAM_INIT) {
+                each([&](int r, double e) {
+                    vr[1][r] = (Acc)(e * (double)vr[0][r]);
+                    vi[1][r] = (Acc)(e * (double)vi[0][r]);
+                });
+                pend[1] = pend[0];
+            }
+            if (fl & PT_GGAMMA) {
+                double gv[1] = {0.0};
+                each([&](int r, double e) {
+                    const Acc q = vr[1][r] * vi[0][r] - vi[1][r] * vr[0][r];
+                    gv[0] += e * (double)q;
+                });
+                gv[0] *= pend[0] * pend[1];
+                block_sums<1, NW>(gv, s_red, put_at(part2));
+            }
+        } else if constexpr (FEAT == 1) {
+            if (fl & PT_ZETA) {
+                const double zt = second ? -opb : opb;
+                each([&](int r, double e) {
+                    const double te = zt * e;
+                    const double pr = (double)vr[0][r], pi = (double)vi[0][r];
+                    vr[0][r] = (Acc)fma(-te, pi, pr);
+                    vi[0][r] = (Acc)fma(te, pr, pi);
+                });
+            }
+            if (fl & PT_EFORM) {
+                double gv[1] = {0.0};
+                each([&](int r, double e) {
+                    const double pr = (double)vr[0][r], pi = (double)vi[0][r];
+                    gv[0] = fma(e, fma(pr, pr, pi * pi), gv[0]);
+                });
+                gv[0] *= pend[0] * pend[0];
+                block_sums<1, NW>(gv, s_red, put_at(part2));
+            }
+        }
+        if (fl & (PT_PHASE_PSI | PT_PHASE_LAM)) {
+            // e^{-i gamma E(r)} = e^{-i gamma E(0)} prod_k e^{-i gamma r_k d_k} e^{-i gamma Q(r)};
+            // lane r of every wave forms the factor of Q(r), which all lanes then read
+            const double2 ql = cis_neg(opa * ka->Q[es][t & (NR - 1)]);
+            double2 gk[R];
+#pragma unroll
+            for (int k = 0; k < R; k++) gk[k] = cis_neg(opa * d[k]);
+            double2 run = cis_neg(opa * e0);
+            if constexpr (NV == 1) {  // long programs: the pending scale does not pile up
+                run.x *= pend[0];
+                run.y *= pend[0];
+                pend[0] = 1.0;
+            }
+#pragma unroll
+            for (int i = 0; i < NR; i++) {
+                const int r = i ^ (i >> 1);
+                if (i > 0) {
+                    const int k = __builtin_ctz(i);
+                    const double gx = gk[k].x, gy = ((r >> k) & 1) ? gk[k].y : -gk[k].y;
+                    run = make_double2(mul_re(run.x, run.y, gx, gy), mul_im(run.x, run.y, gx, gy));
+                }
+                const double qx = lane_value(ql.x, r), qy = lane_value(ql.y, r);
+                const Acc cr = (Acc)mul_re(run.x, run.y, qx, qy), ci = (Acc)mul_im(run.x, run.y, qx, qy);
+#pragma unroll
+                for (int v = 0; v < NV; v++) {
+                    const Acc xr = vr[v][r], xi = vi[v][r];
+                    vr[v][r] = mul_re(xr, xi, cr, ci);
+                    vi[v][r] = mul_im(xr, xi, cr, ci);
+                }
+            }
+        }
+    }
+
+    // ---- store in the current layout
+#pragma unroll
+    for (int v = 0; v < NV; v++) {
+        if (!((a.store >> v) & 1)) continue;
+        V2* __restrict__ dst = reinterpret_cast<V2*>(v == 0 ? a.psi : a.lam) + (base | tg.gmap(thr & ~ph));
+        const Acc sc = (Acc)pend[v];
+#pragma unroll
+        for (int r = 0; r < NR; r++) {
+            const uint32_t ur = (uint32_t)r << ab;
+            if (((thr | ur) & ph) != 0u) continue;
+            V2 x;
+            x.x = (Real)(vr[v][r] * sc);
+            x.y = (Real)(vi[v][r] * sc);
+            dst[tg.gmap(ur)] = x;
+        }
+    }
+}
+
+template <typename Real, typename Acc, int NV, int FEAT>
+static int run_tile(int T, const TileArgs& a, hipStream_t st) {
+    const dim3 grid(a.dual ? 2u : (unsigned)a.ntiles);
+    switch (T) {
+        case 10: hipLaunchKernelGGL((k_tile<Real, Acc, 10, 4, NV, FEAT>), grid, dim3(64), 0, st, a); break;
+        case 11: hipLaunchKernelGGL((k_tile<Real, Acc, 11, 4, NV, FEAT>), grid, dim3(128), 0, st, a); break;
+        case 12: hipLaunchKernelGGL((k_tile<Real, Acc, 12, 4, NV, FEAT>), grid, dim3(256), 0, st, a); break;
+        case 13: hipLaunchKernelGGL((k_tile<Real, Acc, 13, 4, NV, FEAT>), grid, dim3(512), 0, st, a); break;
+        default: return (int)hipErrorInvalidValue;
+    }
+    return (int)hipGetLastError();
+}
+
+template <typename Real, typename Acc>
+static int run_tile_feat(int T, const TileArgs& a, hipStream_t st) {
+    if (a.feat == 0) return run_tile<Real, Acc, 1, 0>(T, a, st);
+    return a.feat == 1 ? run_tile<Real, Acc, 1, 1>(T, a, st) : run_tile<Real, Acc, 1, 2>(T, a, st);
+}
+
+int launch_tile(int dtype, int nv, int T, const TileArgs& a, void* stream) {
+    hipStream_t st = (hipStream_t)stream;
+    if (a.nops < 0 || a.nops > kMaxTileOps || a.nlayouts < 1 || a.nlayouts > kMaxLayouts || a.feat < 0 || a.feat > 2)
+        return (int)hipErrorInvalidValue;
+    if (nv == 2) return dtype == 1 ? run_tile<float, float, 2, 1>(T, a, st) : (int)hipErrorInvalidValue;
+    if (dtype == 2) return run_tile_feat<double, double>(T, a, st);
+    // one workgroup that runs a whole program keeps the amplitudes in double precision
+    return a.resident ? run_tile_feat<float, double>(T, a, st) : run_tile_feat<float, float>(T, a, st);
+}
+
+// Second stage of the reductions of a tile program, one workgroup per result:
+// result i sums its columns of the partial sums ([column][tile]) in a fixed
+// order; a column may be signed by one bit of the tile index (spin
+// expectations of qubits outside the tile).
+__global__ void __launch_bounds__(256) k_gather(const GatherArgs a) {
+    __shared__ double sh[4];
+    const SV_CONST GatherArgs* ka = (const SV_CONST GatherArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    const int i = blockIdx.x, t = threadIdx.x;
+    double v = 0.0;
+    const uint32_t s0 = ka->first[i], s1 = ka->first[i + 1];
+    for (uint32_t s = s0; s < s1; s++) {
+        const uint32_t seg = ka->seg[s];
+        const double* __restrict__ col = a.part + (uint64_t)(seg & 0xffffffu) * a.ntiles;
+        const uint32_t sb = seg >> 24;  // 255: unsigned
+        for (uint32_t w = t; w < a.ntiles; w += 256) {
+            const double x = col[w];
+            v += (sb != 255u && !((w >> sb) & 1u)) ? -x : x;
+        }
+    }
+    v = wave_sum(v);
+    if ((t & 63) == 0) sh[t >> 6] = v;
+    __syncthreads();
+    if (t == 0) a.out[i] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+int launch_gather(const GatherArgs& a, int n, void* stream) {
+    hipLaunchKernelGGL(k_gather, dim3((unsigned)n), dim3(256), 0, (hipStream_t)stream, a);
+    return (int)hipGetLastError();
+}
+
+}  // namespace svk

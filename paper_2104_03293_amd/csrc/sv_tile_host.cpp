@@ -1,0 +1,323 @@
+// libsv host: programs on small tiles (sv_tile.hip), for states that the large
+// tiles cannot spread over the chip.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "sv_host.h"
+
+// Tile bits of a state, 0: the large tiles.  A state of up to 13 qubits is one
+// tile, and its whole program one launch.  Above that the tiles are the
+// smallest that leave two tile groups (T + T - 3 qubits with runs of eight
+// amplitudes), i.e. one pass per layer, which gives 16 to 512 workgroups where
+// the large tiles give 2 to 256.
+int tile_bits(int n, sv_dtype dt) {
+    const int t = knob_for("tile", (int)dt, n);
+    if (t == 0) return 0;
+    if (t > 0) return (t >= 10 && t <= 13 && n <= 2 * t - 3) ? t : 0;
+    if (n <= 13) return std::max(n, 10);
+    if (n > 21) return 0;
+    return std::max(10, (n + 4) / 2);
+}
+
+// Energy table E(z) of an instance (built once, on the caller's stream, which
+// is synchronised so that later launches on any stream may read it).
+static int get_etab(sv_ising_s* H, hipStream_t stream, const double** out, bool lookup_only) {
+    std::lock_guard<std::mutex> g(H->mu);
+    if (!H->d_etab) {
+        if (lookup_only)
+            return fail(SV_ERR_UNSUPPORTED, "the instance has no energy table yet (run sv_qaoa_energy once with a state "
+                                            "of the same n and dtype to build it)");
+        double* d = nullptr;
+        HIPCHECK(hipMalloc(&d, sizeof(double) << H->n));
+        int e = launch_energy_table(ising_dev(H), d, stream);
+        if (e == 0) e = (int)hipStreamSynchronize(stream);
+        if (e != 0) {
+            (void)hipFree(d);
+            return fail(SV_ERR_HIP, "energy table build failed: %s", hipGetErrorString((hipError_t)e));
+        }
+        H->d_etab = d;
+    }
+    *out = H->d_etab;
+    return SV_OK;
+}
+
+// 4 J over the pairs of register bits set in r, for the layout that starts at tile bit b.
+static void register_couplings(const Geometry& geo, const sv_ising_s* H, int b, double* Q) {
+    int slot[64];
+    for (int& x : slot) x = -1;
+    for (int k = 0; k < kTileR; k++) {
+        const int l = b + k;
+        if (l < geo.n) slot[l < geo.c ? l : geo.lo + (l - geo.c)] = k;
+    }
+    for (int e = 0; e < H->m; e++) {
+        const int ka = slot[H->ei[e]], kb = slot[H->ej[e]];
+        if (ka < 0 || kb < 0) continue;
+        for (int r = 0; r < (1 << kTileR); r++)
+            if ((r >> ka & 1) && (r >> kb & 1)) Q[r] += 4.0 * H->J[e];
+    }
+}
+
+// One launch: a list of ops on the tiles of one group.
+struct TileLaunch {
+    int group = 0, nv = 1, load = 1, store = 1;
+    std::vector<TileOp> ops;
+    std::vector<int> layer;  // per op: general layer index or -1
+};
+
+int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, const Plan& plan, bool need_ground,
+                     const FixedScratch* fx, const void* first_src, bool dual) {
+    if (s->failed) return fail(SV_ERR_HIP, "state is in a failed state after an earlier HIP error");
+    const std::vector<Geometry>& groups = plan.by_nv[1];
+    const int T = groups[0].T;
+    const uint64_t ntiles = groups[0].ntiles;
+    const bool single = groups.size() == 1;  // one tile holds the state: results need no second stage
+    double emin = 0.0, etol = 0.0;
+    if (need_ground && H) {
+        if (fx) {
+            std::lock_guard<std::mutex> g(H->mu);
+            if (!H->has_ground)
+                return fail(SV_ERR_UNSUPPORTED, "the instance has no ground-state cache yet (call sv_ground once)");
+        } else {
+            int rc = run_ground(H, s->stream);
+            if (rc) return rc;
+        }
+        emin = H->emin;
+        etol = ground_tol(H);
+    }
+    if (fx) {
+        // the limits of the call (they also bound what the large tiles keep in the fixed region)
+        size_t tab = 0;
+        std::lock_guard<std::mutex> g(H->mu);
+        for (const Pass& p : prog.passes) {
+            tab += p.phase.size() * (32 + (size_t)(H->lut_half >= 0 ? 2 * H->lut_half + 1 : 0));
+            bool point = false;
+            for (const Op& op : p.ops) point = point || op.kind == OP_POINT;
+            if (!H->tile_seen.count(std::make_tuple((int)s->dt, T, p.group, point)))
+                return fail(SV_ERR_UNSUPPORTED, "the instance has no device tables for this n, dtype and plan yet (run "
+                                                "sv_qaoa_energy once with a state of the same n and dtype to build them)");
+        }
+        if (tab > fx->tab_entries)
+            return fail(SV_ERR_UNSUPPORTED, "phase tables need %zu entries, the fixed scratch holds %zu", tab,
+                        fx->tab_entries);
+    }
+
+    // launches and result columns
+    std::vector<TileLaunch> launches;
+    std::vector<std::vector<uint32_t>> segs(std::max(prog.nres, 0));  // per result: its columns (GatherArgs::seg)
+    int ncol = 0, nblk = 0, feat = 0;
+    bool uses_e = false;
+    for (const Pass& p : prog.passes) {
+        // columns of the pass's slots
+        std::vector<int> col(p.slot_dst.size());
+        for (size_t q = 0; q < col.size(); q++) {
+            col[q] = single ? p.slot_dst[q] : ncol++;
+            if (!single) segs[p.slot_dst[q]].push_back((uint32_t)col[q] | 255u << 24);
+        }
+        int spin = -1;
+        if (p.spin_res >= 0) {
+            spin = single ? p.spin_res : ncol;
+            if (!single) {
+                const Geometry& geo = groups[p.group];
+                for (int i = 0; i < s->n; i++) {
+                    const bool in = i < geo.c || (i >= geo.lo && i < geo.lo + geo.g);
+                    const int l = i < geo.c ? i : geo.c + (i - geo.lo);  // tile bit
+                    const int w = i < geo.lo ? i - geo.c : i - geo.g - geo.c;  // bit of the tile index
+                    segs[p.spin_res + i].push_back(in ? (uint32_t)(ncol + l) | 255u << 24
+                                                      : (uint32_t)(ncol + T) | (uint32_t)w << 24);
+                }
+                ncol += T + 1;
+            }
+        }
+        int nops = 0;
+        for (const Op& op : p.ops) nops += op.kind != 0;
+        const bool join = single && !launches.empty() && (int)launches.back().ops.size() + nops <= kMaxTileOps &&
+                          launches.back().nv == p.nv && !p.init;
+        if (!join) {
+            launches.emplace_back();
+            launches.back().group = p.group;
+            launches.back().nv = p.nv;
+            launches.back().load = p.load;
+        }
+        TileLaunch& L = launches.back();
+        L.store = p.store;
+        bool point = false;
+        for (const Op& op : p.ops) {
+            if (op.kind == 0) continue;
+            TileOp o{};
+            o.w0 = (uint32_t)op.kind | (uint32_t)op.flags << 8;
+            o.part = (int16_t)(op.slot >= 0 ? col[op.slot] : -1);
+            o.part2 = (int16_t)(op.slot2 >= 0 ? col[op.slot2] : -1);
+            o.aux = -1;
+            o.a = op.a;
+            o.b = op.b;
+            int layer = -1;
+            if (op.kind == OP_MIX && (op.flags & MIX_GEN)) {
+                layer = op.qidx;
+                o.aux = nblk++;
+                feat |= 2;
+            }
+            if (op.kind == OP_MIX && (op.flags & MIX_GBETA)) feat |= 1;
+            if (op.kind == OP_POINT) {
+                point = true;
+                uses_e = uses_e || H;
+                if (op.flags & PT_SPINZ) {
+                    o.aux = spin;
+                    feat |= 2;
+                }
+                if (op.flags & (PT_ZETA | PT_EFORM | PT_LAM_INIT | PT_GGAMMA)) feat |= 1;
+                if (op.flags & PT_E2) return fail(SV_ERR_UNSUPPORTED, "internal: point op without a small-tile form");
+            }
+            L.ops.push_back(o);
+            L.layer.push_back(layer);
+        }
+        if (H && !fx) {
+            std::lock_guard<std::mutex> g(H->mu);
+            H->tile_seen.insert(std::make_tuple((int)s->dt, T, p.group, point));
+            if (point) H->tile_seen.insert(std::make_tuple((int)s->dt, T, p.group, false));
+        }
+        if (L.nv == 2 && !lam) return fail(SV_ERR_ARG, "internal: two-vector pass without lam");
+    }
+    if (ncol > 32767 || prog.nres * (dual ? 2 : 1) > 32767 || feat == 3)
+        return fail(SV_ERR_UNSUPPORTED, "internal: program does not fit the small tiles");
+    if (dual && (!single || launches.size() != 1))
+        return fail(SV_ERR_UNSUPPORTED, "internal: a paired program needs one launch");
+
+    // workspaces
+    const double* E = nullptr;
+    if (uses_e) {
+        int rc = get_etab(H, s->stream, &E, fx != nullptr);
+        if (rc) return rc;
+    }
+    const size_t part_need = single ? 1 : (size_t)ncol * ntiles;
+    const int nres = prog.nres * (dual ? 2 : 1);
+    double *part = nullptr, *out = nullptr;
+    if (fx) {
+        if (part_need > fx->part_doubles)
+            return fail(SV_ERR_UNSUPPORTED, "reduction partials need %zu doubles, the fixed scratch holds %zu", part_need,
+                        fx->part_doubles);
+        if (nblk > 0) return fail(SV_ERR_UNSUPPORTED, "general layers need allocated scratch");
+        part = fx->part;
+        out = fx->out;
+    } else {
+        int rc = ensure_work(s, part_need, std::max(nres, 1));
+        if (rc) return rc;
+        part = s->w.d_part;
+        // the last stage writes the results to the pinned host buffer (every call that asks for
+        // results waits for the stream before it reads them)
+        out = s->w.h_res;
+        s->w.res_on_host = true;
+    }
+    if (nblk > 0) {
+        if (!prog.layers || prog.nq != s->n) return fail(SV_ERR_ARG, "internal: general layers without matrices");
+        double* h = nullptr;
+        int rc = stage_matrices(s, (size_t)nblk, &h);
+        if (rc) return rc;
+        for (const TileLaunch& L : launches)
+            for (size_t i = 0; i < L.ops.size(); i++) {
+                if (L.layer[i] < 0) continue;
+                const Geometry& geo = groups[L.group];
+                double* blk = h + (size_t)L.ops[i].aux * kGenBlock;
+                for (int l = 0; l < kGenBlock / 8; l++) {
+                    const int q = l < T && l < s->n ? (l < geo.c ? l : geo.lo + (l - geo.c)) : -1;
+                    const double id[8] = {1, 0, 0, 0, 0, 0, 1, 0};
+                    memcpy(blk + 8 * l, q < 0 ? id : prog.layers + ((size_t)L.layer[i] * s->n + q) * 8, 8 * sizeof(double));
+                }
+            }
+        rc = send_matrices(s, (size_t)nblk);
+        if (rc) return rc;
+    }
+
+    for (size_t li = 0; li < launches.size(); li++) {
+        TileLaunch& L = launches[li];
+        const Geometry& geo = groups[L.group];
+        TileArgs a;
+        memset(&a, 0, sizeof(a));
+        a.psi = s->ptr;
+        a.lam = lam ? lam->ptr : nullptr;
+        a.src = li == 0 ? first_src : nullptr;
+        a.part = single ? out : part;
+        a.gmat = s->w.d_gmat;
+        a.ntiles = ntiles;
+        a.n = s->n;
+        a.c = geo.c;
+        a.lo = geo.lo;
+        a.g = geo.g;
+        a.phantom = geo.phantom;
+        a.nlayouts = (int)geo.blocks.size();
+        for (int j = 0; j < a.nlayouts; j++) {
+            a.lbpack |= (uint32_t)geo.blocks[j][0] << (8 * j);
+            a.act_fwd |= geo.act_fwd[j] << (8 * j);
+            a.act_bwd |= geo.act_bwd[j] << (8 * j);
+        }
+        a.load = L.load;
+        a.store = dual ? 0 : L.store;
+        a.nops = (int)L.ops.size();
+        a.swz = knob_for("ldsswz", (int)s->dt, s->n);
+        a.spin_cols = single ? s->n : T + 1;
+        a.dual = dual ? 1 : 0;
+        a.dual_cols = prog.nres;
+        a.resident = single ? 1 : 0;
+        a.feat = L.nv == 2 ? 1 : feat;
+        a.emin = emin;
+        a.etol = etol;
+        a.amp0 = std::pow(2.0, -0.5 * s->n);
+        int cur = 0;
+        for (int i = 0; i < a.nops; i++) {
+            a.ops[i] = L.ops[i];
+            if ((L.ops[i].w0 & 255u) == (uint32_t)OP_MIX) {
+                if (a.nlayouts > 1) cur ^= 1;
+            } else if (H) {
+                a.need_e |= cur ? 2 : 1;
+            }
+        }
+        a.E = E;
+        if (H && a.need_e) {
+            register_couplings(geo, H, geo.blocks[0][0], a.Q[0]);
+            register_couplings(geo, H, geo.blocks[a.nlayouts - 1][0], a.Q[1]);
+        }
+        hipEvent_t ev0;
+        const bool prof = !fx && prof_begin(s->stream, &ev0);
+        const int e = take_injected_failure() ? (int)hipErrorLaunchFailure
+                                              : launch_tile((int)s->dt, L.nv, T, a, s->stream);
+        if (prof) {
+            const int nrd = (a.load & 4) ? 0 : __builtin_popcount(a.load & 3);
+            const int nwr = __builtin_popcount(a.store & 3);
+            prof_end(s->stream, ev0, std::string("pass_") + (s->dt == SV_C128 ? "c128" : "c64") + "_nv" +
+                                         std::to_string(L.nv) + "/T" + std::to_string(T) + "c" + std::to_string(geo.c) +
+                                         (geo.g > 0 ? "o" + std::to_string(geo.lo) : "") + "L" +
+                                         std::to_string(a.nlayouts) + ((a.load & 4) ? "w" : ""),
+                     (double)(nrd + nwr) * (double)s->bytes);
+        }
+        if (e != 0) {
+            s->failed = true;
+            return fail(SV_ERR_HIP, "pass launch failed: %s", hipGetErrorString((hipError_t)e));
+        }
+    }
+    if (single || prog.nres == 0) return SV_OK;
+    for (int r0 = 0; r0 < prog.nres;) {
+        GatherArgs ga;
+        ga.part = part;
+        ga.out = out + r0;
+        ga.ntiles = (uint32_t)ntiles;
+        int n = 0, k = 0;
+        while (r0 + n < prog.nres && n < 256 && k + (int)segs[r0 + n].size() <= 768) {
+            ga.first[n] = (uint16_t)k;
+            for (uint32_t sg : segs[r0 + n]) ga.seg[k++] = sg;
+            n++;
+        }
+        if (n == 0) return fail(SV_ERR_UNSUPPORTED, "internal: a result with too many columns");
+        ga.first[n] = (uint16_t)k;
+        const int e = launch_gather(ga, n, s->stream);
+        if (e != 0) {
+            s->failed = true;
+            return fail(SV_ERR_HIP, "reduce launch failed: %s", hipGetErrorString((hipError_t)e));
+        }
+        r0 += n;
+    }
+    return SV_OK;
+}

@@ -241,8 +241,7 @@ constexpr int kMaxTileOps = 104;
 constexpr double kTileMaxAngle = 65536.0;  // phase angles gamma * E beyond it use the large tiles
 struct TileOp {
     uint32_t w0;   // OpKind | MixFlags / PointFlags << 8
-    int16_t part;  // MIX_GBETA, PT_REDUCE: first column
-    int16_t part2; // PT_GGAMMA, PT_EFORM: column
+    uint32_t parts;  // low half: MIX_GBETA, PT_REDUCE: first column; high half: PT_GGAMMA, PT_EFORM: column
     int32_t aux;   // MIX_GEN: matrix block; PT_SPINZ: first column
     int32_t pad;
     double a, b;   // as Op::a, Op::b
@@ -263,7 +262,6 @@ struct TileArgs {
     int32_t load, store;    // as PassArgs
     int32_t need_e;         // bit 0: a point op runs in layout 0, bit 1: in the last layout
     int32_t nops;
-    int32_t swz;
     int32_t spin_cols;      // columns of a PT_SPINZ op (T + 1, or n where one tile holds the state)
     int32_t dual;           // two workgroups run the program with PT_ZETA's t and -t, the second
     int32_t dual_cols;      //   writing its columns dual_cols further on

@@ -12,8 +12,11 @@
 // phase factors are computed in place instead of by a launch of their own, and
 // the code is a loop over ops and layouts (one copy of each op's code).
 // Measured against the large tiles: n = 12 complex64, p = 4 (one launch) 93 ->
-// 24 us per evaluation, n = 18 complex128, p = 8 184 -> 117 us (passes of 15-22
-// us -> 12-14 us), n = 21 real couplings, p = 3 171 -> 95 us.
+// 20 us per evaluation, n = 20 complex64, p = 8 255 -> 132 us, n = 21 real
+// couplings, p = 3 164 -> 92 us, n = 17 gradient, p = 4 436 -> 159 us.  Cycle
+// stamps of one workgroup (n = 18, 2^11 tiles): start and loads 2500, a mixer
+// round 900 of arithmetic and 1300 of exchange, a phase 2700, a reduction 2300,
+// store 900.
 #include <hip/hip_runtime.h>
 
 #include "sv_device.h"
@@ -87,10 +90,22 @@ __device__ __forceinline__ X mul_im(X ar, X ai, X br, X bi) {
     return fma(ar, bi, ai * br);
 }
 
+// Wave sum, the same in every lane: within rows of 16 by DPP moves (lane ^ 1, lane ^ 2, mirrored
+// halves, mirrored row), then the four rows as scalars.  A third of the latency of six
+// cross-lane reads through LDS.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return v + __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    v = dpp_add<0xB1>(v);   // quad_perm 1 0 3 2
+    v = dpp_add<0x4E>(v);   // quad_perm 2 3 0 1
+    v = dpp_add<0x141>(v);  // row_half_mirror
+    v = dpp_add<0x140>(v);  // row_mirror
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
 // Workgroup sums of N per-thread values in a fixed order, handed to
@@ -119,6 +134,11 @@ __device__ __forceinline__ void block_sums(double (&v)[N], double (*s_red)[kTF],
     }
 }
 
+// LDS slot of a tile-local index (T <= 16): the higher nibbles folded into the lowest one, and the
+// slot bits of one index bit (both linear over XOR).
+__device__ __forceinline__ uint32_t tile_slot(uint32_t u) { return u ^ (((u >> 4) ^ (u >> 8) ^ (u >> 12)) & 15u); }
+__device__ __forceinline__ uint32_t tile_slot_bit(int p) { return (1u << p) | (p >= 4 ? 1u << (p & 3) : 0u); }
+
 // One tile program.  Real: stored amplitudes; Acc: amplitudes in registers and
 // LDS; 2^T amplitudes per workgroup, 2^R per thread and vector, NV vectors.
 // Layout j holds tile bits [lb[j], lb[j] + R) in registers and the others in
@@ -136,10 +156,21 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
     __shared__ A2 xbuf[1 << T];
     __shared__ double s_red[NW][kTF];
 
+    // every scalar of the header at once (the compiler would fetch them block by block, a memory
+    // round trip each)
+    asm volatile("" ::"s"(a.psi), "s"(a.lam), "s"(a.src), "s"(a.E), "s"(a.part), "s"(a.c), "s"(a.lo), "s"(a.g));
+    asm volatile("" ::"s"(a.phantom), "s"(a.nlayouts), "s"(a.lbpack), "s"(a.act_fwd), "s"(a.act_bwd), "s"(a.load),
+                 "s"(a.store), "s"(a.need_e), "s"(a.nops), "s"(a.dual), "s"(a.amp0));
     const uint32_t t = threadIdx.x;
     // the op list is read where it lies (a dynamic index into a by-value
     // argument would copy it to scratch memory)
     const SV_CONST TileArgs* ka = (const SV_CONST TileArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    struct {
+        uint32_t w0, parts;
+        int aux;
+        double a, b;
+    } op0 = {ka->ops[0].w0, ka->ops[0].parts, ka->ops[0].aux, ka->ops[0].a, ka->ops[0].b};
+    asm volatile("" ::"s"(op0.w0), "s"(op0.parts), "s"(op0.aux), "s"(op0.a), "s"(op0.b));
     const uint64_t tile = a.dual ? 0 : blockIdx.x;
     const bool second = a.dual && blockIdx.x != 0;
     const TileGeom tg{a.c, a.lo, a.g};
@@ -154,47 +185,69 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
     int ab = lbase(0);
     uint32_t thr = tpart(ab);
 
+    // Byte offsets of 32 bits (the states here hold less than 2^28 bytes); register r = i ^ (i >> 1)
+    // is reached by one XOR from register (i - 1) ^ ((i - 1) >> 1).
+    constexpr uint32_t ES = (uint32_t)sizeof(V2);
+    auto goff = [&](uint32_t u) { return (uint32_t)tg.gmap(u & ~ph); };
+    const uint32_t base32 = (uint32_t)base;
+
     // ---- load in layout 0
     Acc vr[NV][NR], vi[NV][NR];
     {
-        const uint64_t off = base | tg.gmap(thr & ~ph);
+        uint32_t gb[R];
+#pragma unroll
+        for (int k = 0; k < R; k++) gb[k] = goff(1u << (ab + k)) * ES;
 #pragma unroll
         for (int v = 0; v < NV; v++) {
-            const V2* __restrict__ src =
-                reinterpret_cast<const V2*>(v == 1 ? a.lam : (a.src ? a.src : a.psi)) + off;
-            const bool ld = (a.load >> v) & 1;
+            const char* __restrict__ src =
+                reinterpret_cast<const char*>(v == 1 ? (const void*)a.lam : (a.src ? a.src : (const void*)a.psi));
+            if ((a.load >> v) & 1) {
+                uint32_t off = (base32 | goff(thr)) * ES;
 #pragma unroll
-            for (int r = 0; r < NR; r++) {
-                const uint32_t ur = (uint32_t)r << ab;
-                Acc xr = 0, xi = 0;
-                if (((thr | ur) & ph) == 0u) {
-                    if (ld) {
-                        const V2 x = src[tg.gmap(ur)];
-                        xr = x.x;
-                        xi = x.y;
-                    } else if (v == 0 && (a.load & 4)) {
-                        xr = (Acc)a.amp0;
-                    }
+                for (int i = 0; i < NR; i++) {
+                    if (i > 0) off ^= gb[__builtin_ctz(i)];
+                    const int r = i ^ (i >> 1);
+                    const V2 x = *reinterpret_cast<const V2*>(src + off);
+                    vr[v][r] = x.x;
+                    vi[v][r] = x.y;
                 }
-                vr[v][r] = xr;
-                vi[v][r] = xi;
+            } else {
+                const Acc x0 = (v == 0 && (a.load & 4)) ? (Acc)a.amp0 : (Acc)0;
+#pragma unroll
+                for (int r = 0; r < NR; r++) {
+                    vr[v][r] = x0;
+                    vi[v][r] = 0;
+                }
+            }
+            if (ph != 0u) {  // states smaller than the tile
+#pragma unroll
+                for (int r = 0; r < NR; r++) {
+                    const bool valid = ((thr | ((uint32_t)r << ab)) & ph) == 0u;
+                    vr[v][r] = valid ? vr[v][r] : (Acc)0;
+                    vi[v][r] = valid ? vi[v][r] : (Acc)0;
+                }
             }
         }
     }
     // energies of the thread's register 0 and of the registers one bit away from
-    // it, for the layouts that hold a point op: E(r) = E(0) + sum_k r_k d_k + Q(r)
-    double ev[2][R + 1];
+    // it, for the layouts that hold a point op: E(r) = E(0) + sum_k r_k d_k + Q(r);
+    // lane r also takes Q(r)
+    double ev[2][R + 1], ql[2];
 #pragma unroll
     for (int s = 0; s < 2; s++) {
 #pragma unroll
         for (int k = 0; k <= R; k++) ev[s][k] = 0.0;
+        ql[s] = 0.0;
         if ((a.need_e >> s) & 1) {
             const int b = lbase(s ? K - 1 : 0);
-            const uint32_t u = tpart(b) & ~ph;
-            const double* __restrict__ E = a.E + base;
-            ev[s][0] = E[tg.gmap(u)];
+            const uint32_t u = tpart(b);
+            const char* __restrict__ E = reinterpret_cast<const char*>(a.E);
+            const uint32_t o = (base32 | goff(u)) * 8u;
+            ev[s][0] = *reinterpret_cast<const double*>(E + o);
 #pragma unroll
-            for (int k = 0; k < R; k++) ev[s][1 + k] = E[tg.gmap((u | (1u << (b + k))) & ~ph)];
+            for (int k = 0; k < R; k++)
+                ev[s][1 + k] = *reinterpret_cast<const double*>(E + (o ^ (goff(1u << (b + k)) * 8u)));
+            ql[s] = ka->Q[s][t & (NR - 1)];
         }
     }
 
@@ -202,12 +255,25 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
 #pragma unroll
     for (int v = 0; v < NV; v++) pend[v] = 1.0;
 
+    // the next op is fetched while one runs
+    uint32_t nw0 = op0.w0;
+    uint32_t nparts = op0.parts;
+    int naux = op0.aux;
+    double na = op0.a, nb_ = op0.b;
 #pragma unroll 1
     for (int oi = 0; oi < a.nops; oi++) {
-        const uint32_t w0 = ka->ops[oi].w0;
+        const uint32_t w0 = nw0;
         const int kind = (int)(w0 & 255u), fl = (int)(w0 >> 8);
-        const double opa = ka->ops[oi].a, opb = ka->ops[oi].b;
-        const int part0 = ka->ops[oi].part, part2 = ka->ops[oi].part2, aux = ka->ops[oi].aux;
+        const double opa = na, opb = nb_;
+        const int part0 = (int)(int16_t)(nparts & 0xffffu), part2 = (int)nparts >> 16, aux = naux;
+        {
+            const SV_CONST TileOp* nx = &ka->ops[oi + 1 < a.nops ? oi + 1 : oi];
+            nw0 = nx->w0;
+            nparts = nx->parts;
+            naux = nx->aux;
+            na = nx->a;
+            nb_ = nx->b;
+        }
         auto put_at = [&](int col) {
             return [&, col](int i, double x) { part[(uint64_t)(col + i) * a.ntiles + tile] = x; };
         };
@@ -227,10 +293,10 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
                     uint32_t bs[R], bd[R];
 #pragma unroll
                     for (int k = 0; k < R; k++) {
-                        bs[k] = lds_swizzle(1u << (ab + k), a.swz) * SZ;
-                        bd[k] = lds_swizzle(1u << (nb + k), a.swz) * SZ;
+                        bs[k] = tile_slot_bit(ab + k) * SZ;
+                        bd[k] = tile_slot_bit(nb + k) * SZ;
                     }
-                    const uint32_t s0 = lds_swizzle(thr, a.swz) * SZ, d0 = lds_swizzle(nthr, a.swz) * SZ;
+                    const uint32_t s0 = tile_slot(thr) * SZ, d0 = tile_slot(nthr) * SZ;
                     char* xb = reinterpret_cast<char*>(xbuf);
 #pragma unroll
                     for (int v = 0; v < NV; v++) {
@@ -285,8 +351,11 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
                 }
 #pragma unroll
                 for (int k = 0; k < R; k++) {
-                    if (!((act >> k) & 1)) continue;
-                    if (NV == 2 && FEAT == 1 && (fl & MIX_GBETA)) {
+                    // a slot that is not active here runs identity butterflies (t = 0): a branch
+                    // would copy the amplitude registers at its join
+                    const bool on = (act >> k) & 1;
+                    const Acc tk = on ? tq : (Acc)0;
+                    if (on && NV == 2 && FEAT == 1 && (fl & MIX_GBETA)) {
                         // Im(conj(lam_a) psi_b) + Im(conj(lam_b) psi_a), summed in FP64
                         double gb = 0.0;
 #pragma unroll
@@ -301,14 +370,15 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
                     }
 #pragma unroll
                     for (int v = 0; v < NV; v++) {
-                        if (NV == 2 && !(fl & (1 << v))) continue;
+                        const bool mine = NV == 1 || (fl & (1 << v)) != 0;
+                        const Acc tv = mine ? tk : (Acc)0;
 #pragma unroll
                         for (int r = 0; r < NR; r++) {
                             if (r & (1 << k)) continue;
                             const int r2 = r | (1 << k);
-                            butterfly<Acc>(vr[v][r], vi[v][r], vr[v][r2], vi[v][r2], tq);
+                            butterfly<Acc>(vr[v][r], vi[v][r], vr[v][r2], vi[v][r2], tv);
                         }
-                        pend[v] *= opb;
+                        pend[v] *= (on && mine) ? opb : 1.0;
                     }
                 }
                 if (FEAT == 1 && NV == 1 && (fl & MIX_GBETA)) {
@@ -350,7 +420,7 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
                     const int k = __builtin_ctz(i);
                     e_run += ((r >> k) & 1) ? d[k] : -d[k];
                 }
-                f(r, e_run + ka->Q[es][r]);
+                f(r, e_run + lane_value(es ? ql[1] : ql[0], r));
             }
         };
         if (fl & (PT_REDUCE | PT_SPINZ)) {
@@ -436,7 +506,7 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
         if (fl & (PT_PHASE_PSI | PT_PHASE_LAM)) {
             // e^{-i gamma E(r)} = e^{-i gamma E(0)} prod_k e^{-i gamma r_k d_k} e^{-i gamma Q(r)};
             // lane r of every wave forms the factor of Q(r), which all lanes then read
-            const double2 ql = cis_neg(opa * ka->Q[es][t & (NR - 1)]);
+            const double2 qf = cis_neg(opa * (es ? ql[1] : ql[0]));
             double2 gk[R];
 #pragma unroll
             for (int k = 0; k < R; k++) gk[k] = cis_neg(opa * d[k]);
@@ -454,7 +524,7 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
                     const double gx = gk[k].x, gy = ((r >> k) & 1) ? gk[k].y : -gk[k].y;
                     run = make_double2(mul_re(run.x, run.y, gx, gy), mul_im(run.x, run.y, gx, gy));
                 }
-                const double qx = lane_value(ql.x, r), qy = lane_value(ql.y, r);
+                const double qx = lane_value(qf.x, r), qy = lane_value(qf.y, r);
                 const Acc cr = (Acc)mul_re(run.x, run.y, qx, qy), ci = (Acc)mul_im(run.x, run.y, qx, qy);
 #pragma unroll
                 for (int v = 0; v < NV; v++) {
@@ -467,19 +537,37 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
     }
 
     // ---- store in the current layout
+    {
+        uint32_t gb[R];
 #pragma unroll
-    for (int v = 0; v < NV; v++) {
-        if (!((a.store >> v) & 1)) continue;
-        V2* __restrict__ dst = reinterpret_cast<V2*>(v == 0 ? a.psi : a.lam) + (base | tg.gmap(thr & ~ph));
-        const Acc sc = (Acc)pend[v];
+        for (int k = 0; k < R; k++) gb[k] = goff(1u << (ab + k)) * ES;
 #pragma unroll
-        for (int r = 0; r < NR; r++) {
-            const uint32_t ur = (uint32_t)r << ab;
-            if (((thr | ur) & ph) != 0u) continue;
-            V2 x;
-            x.x = (Real)(vr[v][r] * sc);
-            x.y = (Real)(vi[v][r] * sc);
-            dst[tg.gmap(ur)] = x;
+        for (int v = 0; v < NV; v++) {
+            if (!((a.store >> v) & 1)) continue;
+            char* __restrict__ dst = reinterpret_cast<char*>(v == 0 ? a.psi : a.lam);
+            const Acc sc = (Acc)pend[v];
+            uint32_t off = (base32 | goff(thr)) * ES;
+            if (ph == 0u) {
+#pragma unroll
+                for (int i = 0; i < NR; i++) {
+                    if (i > 0) off ^= gb[__builtin_ctz(i)];
+                    const int r = i ^ (i >> 1);
+                    V2 x;
+                    x.x = (Real)(vr[v][r] * sc);
+                    x.y = (Real)(vi[v][r] * sc);
+                    *reinterpret_cast<V2*>(dst + off) = x;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < NR; r++) {
+                    const uint32_t ur = (uint32_t)r << ab;
+                    if (((thr | ur) & ph) != 0u) continue;
+                    V2 x;
+                    x.x = (Real)(vr[v][r] * sc);
+                    x.y = (Real)(vi[v][r] * sc);
+                    *reinterpret_cast<V2*>(dst + (off ^ (goff(ur) * ES))) = x;
+                }
+            }
         }
     }
 }

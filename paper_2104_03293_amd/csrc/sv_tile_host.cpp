@@ -150,8 +150,8 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
             if (op.kind == 0) continue;
             TileOp o{};
             o.w0 = (uint32_t)op.kind | (uint32_t)op.flags << 8;
-            o.part = (int16_t)(op.slot >= 0 ? col[op.slot] : -1);
-            o.part2 = (int16_t)(op.slot2 >= 0 ? col[op.slot2] : -1);
+            o.parts = ((uint32_t)(op.slot >= 0 ? col[op.slot] : 0) & 0xffffu) |
+                      (uint32_t)(op.slot2 >= 0 ? col[op.slot2] : 0) << 16;
             o.aux = -1;
             o.a = op.a;
             o.b = op.b;
@@ -257,7 +257,6 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
         a.load = L.load;
         a.store = dual ? 0 : L.store;
         a.nops = (int)L.ops.size();
-        a.swz = knob_for("ldsswz", (int)s->dt, s->n);
         a.spin_cols = single ? s->n : T + 1;
         a.dual = dual ? 1 : 0;
         a.dual_cols = prog.nres;

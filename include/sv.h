@@ -269,13 +269,16 @@ int sv_schedule_second_order(int p, double tau, const double* A, const double* B
                              double* gamma, double* beta);
 
 /* ----------------------------------------------------------------- batch --
- * p = 1 landscape scan (Sec. III.C.1, Fig. 5) over many small instances in
- * persistent launches: for every instance i and grid point (gamma_a, beta_b)
+ * p = 1 landscape scan (Sec. III.C.1, Fig. 5) over many small instances: for every instance i and grid point (gamma_a, beta_b)
  * evaluate |psi> = exp(-i beta_b H_D) exp(-i gamma_a H_C_i) |+>^{n_i} and write
  *   energy_out[(i * n_gamma + a) * n_beta + b] = <H_C_i>
  *   pgs_out   [(i * n_gamma + a) * n_beta + b] = ground-state probability.
  * Instances may differ in n (1..19 for SV_C64, 1..18 for SV_C128; larger n
- * returns SV_ERR_UNSUPPORTED).  dtype selects the amplitude storage.
+ * returns SV_ERR_UNSUPPORTED).  dtype selects the amplitude storage; instances
+ * whose h and J lie on a grid Z / q (q = 1, 2, 4; small integers, half-integers)
+ * are evaluated without amplitudes, in FP64 for either dtype (closed forms of
+ * <H_C>, sums over the Hamming spheres around each ground state for P_gs), unless
+ * they have more ground states than grid points (or more than 4096).
  * Outputs are host arrays.  Runs on the given stream; synchronises. */
 int sv_batch_p1_scan(int n_inst, const sv_ising* insts, int n_gamma, const double* gammas,
                      int n_beta, const double* betas, sv_dtype dtype, void* hip_stream,

@@ -1023,7 +1023,7 @@ extern "C" int sv_tune_describe(int n, sv_dtype dtype, char* buf, size_t len) {
         bool first = true;
         for (const std::string& k : names) {
             // the values a plan for this (dtype, n) uses: tuned overrides over the global knobs
-            const int nsz = (k == "batchwide" || k == "batch128" || k == "batchslab") ? 0 : n;
+            const int nsz = (k == "batchwide" || k == "batch128" || k == "batchslab" || k == "batchsphere") ? 0 : n;
             js += (first ? "" : ",") + std::string("\"") + k + "\":" + std::to_string(knob_for(k.c_str(), (int)dtype, nsz));
             first = false;
         }

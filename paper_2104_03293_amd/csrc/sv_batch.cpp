@@ -17,22 +17,13 @@
 #include "sv_host.h"
 
 // ============================================================================ batch scan
-extern "C" int sv_batch_p1_scan(int n_inst, const sv_ising* insts, int n_gamma, const double* gammas, int n_beta,
-                                const double* betas, sv_dtype dtype, void* stream, double* energy_out,
-                                double* pgs_out) {
-    if (n_inst < 1 || !insts) return fail(SV_ERR_ARG, "sv_batch_p1_scan: no instances");
-    if (n_gamma < 1 || n_beta < 1 || !gammas || !betas) return fail(SV_ERR_ARG, "sv_batch_p1_scan: empty grid");
-    if (!energy_out || !pgs_out) return fail(SV_ERR_ARG, "sv_batch_p1_scan: NULL output");
-    if (!dtype_ok(dtype)) return fail(SV_ERR_ARG, "sv_batch_p1_scan: bad dtype");
-    if ((int64_t)n_gamma * n_beta > (1 << 24)) return fail(SV_ERR_ARG, "sv_batch_p1_scan: grid too large");
-    for (int a = 0; a < n_gamma; a++)
-        if (!std::isfinite(gammas[a])) return fail(SV_ERR_NUMERIC, "sv_batch_p1_scan: gamma %d not finite", a);
-    for (int b = 0; b < n_beta; b++)
-        if (!std::isfinite(betas[b])) return fail(SV_ERR_NUMERIC, "sv_batch_p1_scan: beta %d not finite", b);
+// Direct scan: every grid point of every instance mixes its 2^n amplitudes.  Outputs of
+// instance i start at n_gamma * n_beta * i.
+static int direct_scan(int n_inst, const sv_ising* insts, int n_gamma, const double* gammas, int n_beta,
+                       const double* betas, sv_dtype dtype, void* stream, double* energy_out, double* pgs_out) {
     const int wide = dtype == SV_C64 ? knob_for("batchwide", (int)dtype, 0) : knob_for("batch128", (int)dtype, 0);
     const int lut_cap = batch_lut_cap((int)dtype, wide);
     const int S = batch_lds_bits((int)dtype, wide);
-    const int nmax_batch = S + 5;  // the high bits of a state fit one thread's 32 registers
     std::vector<BatchInst> bi(n_inst);
     std::vector<double> hh, JJ;
     std::vector<int32_t> ii, jj;
@@ -40,9 +31,6 @@ extern "C" int sv_batch_p1_scan(int n_inst, const sv_ising* insts, int n_gamma, 
     int max_n = 1;
     for (int i = 0; i < n_inst; i++) {
         const sv_ising_s* H = insts[i];
-        if (!H) return fail(SV_ERR_ARG, "sv_batch_p1_scan: instance %d is NULL", i);
-        if (H->n > nmax_batch)
-            return fail(SV_ERR_UNSUPPORTED, "sv_batch_p1_scan: instance %d has n=%d > %d", i, H->n, nmax_batch);
         BatchInst& b = bi[i];
         b.n = H->n;
         b.m = H->m;
@@ -239,3 +227,243 @@ extern "C" int sv_batch_p1_scan(int n_inst, const sv_ising* insts, int n_gamma, 
     return SV_OK;
 }
 
+// Device memory of one scan: one allocation, carved up, freed with the object.
+namespace {
+struct Arena {
+    char* base = nullptr;
+    size_t used = 0;
+    size_t take(size_t bytes) {
+        const size_t at = used;
+        used += (bytes + 255) & ~size_t(255);
+        return at;
+    }
+    bool alloc() {
+        if (hipMalloc(&base, std::max<size_t>(used, 256)) == hipSuccess) return true;
+        (void)hipGetLastError();
+        base = nullptr;
+        return false;
+    }
+    template <typename X>
+    X* at(size_t off) const {
+        return reinterpret_cast<X*>(base + off);
+    }
+    ~Arena() {
+        if (base) (void)hipFree(base);
+    }
+};
+}  // namespace
+
+// The instances an energy grid and their table sizes allow the sphere sums for.
+static bool scan_by_spheres(const sv_ising_s* H) {
+    if (H->qden <= 0 || H->n > kScanMaxN) return false;
+    const double L = H->qden * H->scale;
+    return (H->n + 1) * (2.0 * L + 1.0) * 4.0 <= (double)kScanMaxLds;
+}
+
+// Scan by sphere sums (sv_scan.hip) of instances idx[].  done[k] = 0 for those with too many
+// ground states, which are left to the direct scan.
+static int sphere_scan(const std::vector<int>& idx, const sv_ising* insts, int n_gamma, const double* gammas,
+                       int n_beta, const double* betas, hipStream_t st, double* energy_out, double* pgs_out,
+                       std::vector<char>& done) {
+    const int ni = (int)idx.size();
+    const size_t pts = (size_t)n_gamma * n_beta;
+    // A ground state costs one pass over 2^n indices, a grid point of the direct scan n mixer
+    // passes over 2^n amplitudes: as many ground states as grid points are taken (at most 4096,
+    // which bounds the list).
+    const size_t zmax = std::min<size_t>(pts, 4096);
+    std::vector<ScanInst> si(ni);
+    std::vector<int32_t> hq, cq, stat(3 * (size_t)ni);
+    uint64_t xtot = 0;
+    int64_t ztot = 0;
+    int max_n = 1;
+    for (int k = 0; k < ni; k++) {
+        const sv_ising_s* H = insts[idx[k]];
+        ScanInst& s = si[k];
+        s.n = H->n;
+        s.m = H->m;
+        s.hoff = (int32_t)hq.size();
+        s.coff = (int32_t)(cq.size() / 3);
+        s.xoff = xtot;
+        s.q = H->qden;
+        s.lo = -(int32_t)std::lround(H->qden * H->scale);
+        s.zcap = (int32_t)std::min<size_t>(zmax, size_t(1) << H->n);
+        s.zoff = ztot;
+        s.out = idx[k];
+        xtot += std::max<uint64_t>(8, 1ull << H->n);
+        ztot += s.zcap;
+        max_n = std::max(max_n, H->n);
+        for (double v : H->h) hq.push_back((int32_t)std::lround(v * H->qden));
+        for (int e = 0; e < H->m; e++) {
+            cq.push_back(H->ei[e]);
+            cq.push_back(H->ej[e]);
+            cq.push_back((int32_t)std::lround(H->J[e] * H->qden));
+        }
+        stat[3 * (size_t)k] = INT32_MAX;
+        stat[3 * (size_t)k + 1] = -1;
+        stat[3 * (size_t)k + 2] = 0;
+    }
+    // one allocation: inputs (copied in one go), tables, outputs
+    Arena ar;
+    const size_t o_inst = ar.take(ni * sizeof(ScanInst)), o_h = ar.take(hq.size() * 4), o_c = ar.take(cq.size() * 4),
+                 o_stat = ar.take(stat.size() * 4), o_g = ar.take(n_gamma * sizeof(double)),
+                 o_b = ar.take(n_beta * sizeof(double));
+    const size_t in_bytes = ar.used;
+    const size_t o_x = ar.take(xtot * 2), o_z = ar.take((size_t)ztot * 4),
+                 o_coef = ar.take((size_t)ni * n_gamma * 3 * sizeof(double));
+    const size_t nout = (size_t)ni * pts;
+    const size_t o_e = ar.take(nout * sizeof(double)), o_p = ar.take(nout * sizeof(double));
+    if (!ar.alloc()) return fail(SV_ERR_OOM, "sv_batch_p1_scan: device allocation failed");
+    std::vector<char> blob(in_bytes);
+    memcpy(blob.data() + o_inst, si.data(), ni * sizeof(ScanInst));
+    for (int k = 0; k < ni; k++) reinterpret_cast<ScanInst*>(blob.data() + o_inst)[k].out = k;
+    memcpy(blob.data() + o_h, hq.data(), hq.size() * 4);
+    if (!cq.empty()) memcpy(blob.data() + o_c, cq.data(), cq.size() * 4);
+    memcpy(blob.data() + o_stat, stat.data(), stat.size() * 4);
+    memcpy(blob.data() + o_g, gammas, n_gamma * sizeof(double));
+    memcpy(blob.data() + o_b, betas, n_beta * sizeof(double));
+    hipError_t e = hipMemcpyAsync(ar.base, blob.data(), in_bytes, hipMemcpyHostToDevice, st);
+    ScanArgs a;
+    memset(&a, 0, sizeof(a));
+    a.inst = ar.at<ScanInst>(o_inst);
+    a.hq = ar.at<int32_t>(o_h);
+    a.cq = ar.at<int32_t>(o_c);
+    a.x = ar.at<uint16_t>(o_x);
+    a.stat = ar.at<int32_t>(o_stat);
+    a.z = ar.at<uint32_t>(o_z);
+    a.coef = ar.at<double>(o_coef);
+    a.gammas = ar.at<double>(o_g);
+    a.betas = ar.at<double>(o_b);
+    a.out_e = ar.at<double>(o_e);
+    a.out_p = ar.at<double>(o_p);
+    a.ng = n_gamma;
+    a.nb = n_beta;
+    a.bpi = (uint32_t)std::min(32, std::max(1, (1 << max_n) / (256 * 8)));
+    a.gpb = (uint32_t)((n_gamma + 3) / 4);
+    int ke = 0;
+    if (e == hipSuccess) ke = launch_scan_tables(a, ni, st);
+    if (e == hipSuccess && !ke)
+        e = hipMemcpyAsync(stat.data(), a.stat, stat.size() * 4, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && !ke) e = hipStreamSynchronize(st);
+    if (ke || e != hipSuccess)
+        return fail(SV_ERR_HIP, "sv_batch_p1_scan: %s", hipGetErrorString(ke ? (hipError_t)ke : e));
+    // units: the ground states of the instances taken, largest states first
+    std::vector<int> order(ni);
+    for (int k = 0; k < ni; k++) order[k] = k;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return si[x].n > si[y].n; });
+    std::vector<int32_t> uinst, oinst;
+    std::vector<int64_t> uoff(ni, 0);
+    size_t lds = 0;
+    for (int k : order) {
+        done[k] = stat[3 * (size_t)k + 2] <= si[k].zcap;
+        if (!done[k]) continue;
+        uoff[k] = (int64_t)uinst.size();
+        uinst.insert(uinst.end(), (size_t)stat[3 * (size_t)k + 2], k);
+        oinst.push_back(k);
+        lds = std::max(lds, (size_t)(si[k].n + 1) * (stat[3 * (size_t)k + 1] - stat[3 * (size_t)k] + 1) * 4);
+    }
+    if (uinst.empty()) return SV_OK;
+    // sphere sums of a launch: up to 1024 gammas, and as many ground states as fit 64 MiB
+    const int gc = std::min(n_gamma, 1024);
+    const size_t per_unit = (size_t)gc * (kScanMaxN + 1) * sizeof(double2);
+    const int64_t units_max =
+        std::max<int64_t>(1, std::min<int64_t>((int64_t)uinst.size(), (int64_t)((size_t(64) << 20) / per_unit)));
+    Arena au;
+    const size_t o_uoff = au.take(ni * sizeof(int64_t)), o_oinst = au.take(oinst.size() * 4),
+                 o_uinst = au.take(uinst.size() * 4);
+    const size_t u_bytes = au.used, o_amps = au.take((size_t)units_max * per_unit);
+    if (!au.alloc()) return fail(SV_ERR_OOM, "sv_batch_p1_scan: device allocation failed");
+    blob.assign(u_bytes, 0);
+    memcpy(blob.data() + o_uoff, uoff.data(), ni * sizeof(int64_t));
+    memcpy(blob.data() + o_oinst, oinst.data(), oinst.size() * 4);
+    memcpy(blob.data() + o_uinst, uinst.data(), uinst.size() * 4);
+    a.amps = au.at<double2>(o_amps);
+    a.uinst = au.at<int32_t>(o_uinst);
+    a.uoff = au.at<int64_t>(o_uoff);
+    a.oinst = au.at<int32_t>(o_oinst);
+    e = hipMemcpyAsync(au.base, blob.data(), u_bytes, hipMemcpyHostToDevice, st);
+    for (int64_t g0 = 0; g0 < n_gamma && e == hipSuccess && !ke; g0 += gc) {
+        a.g0 = g0;
+        a.gc = (int32_t)std::min<int64_t>(gc, n_gamma - g0);
+        size_t first = 0;  // first entry of oinst that still has units
+        for (int64_t u0 = 0; u0 < (int64_t)uinst.size() && !ke; u0 += units_max) {
+            a.u0 = u0;
+            a.ucount = std::min<int64_t>(units_max, (int64_t)uinst.size() - u0);
+            while (uoff[oinst[first]] + stat[3 * (size_t)oinst[first] + 2] <= u0) first++;
+            size_t last = first;
+            while (last < oinst.size() && uoff[oinst[last]] < u0 + a.ucount) last++;
+            a.o0 = (uint32_t)first;
+            ke = launch_scan_points(a, (int)(last - first), lds, st);
+        }
+    }
+    std::vector<double> tmp;
+    const bool whole = ni == (int)done.size() && oinst.size() == (size_t)ni && idx.back() == ni - 1;
+    double *oe = energy_out, *op = pgs_out;
+    if (!whole) {
+        tmp.resize(2 * nout);
+        oe = tmp.data();
+        op = tmp.data() + nout;
+    }
+    if (e == hipSuccess && !ke) e = hipMemcpyAsync(oe, a.out_e, nout * sizeof(double), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && !ke) e = hipMemcpyAsync(op, a.out_p, nout * sizeof(double), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && !ke) e = hipStreamSynchronize(st);
+    if (ke || e != hipSuccess)
+        return fail(SV_ERR_HIP, "sv_batch_p1_scan: %s", hipGetErrorString(ke ? (hipError_t)ke : e));
+    if (!whole)
+        for (int k = 0; k < ni; k++) {
+            if (!done[k]) continue;
+            memcpy(energy_out + (size_t)idx[k] * pts, oe + (size_t)k * pts, pts * sizeof(double));
+            memcpy(pgs_out + (size_t)idx[k] * pts, op + (size_t)k * pts, pts * sizeof(double));
+        }
+    return SV_OK;
+}
+
+extern "C" int sv_batch_p1_scan(int n_inst, const sv_ising* insts, int n_gamma, const double* gammas, int n_beta,
+                                const double* betas, sv_dtype dtype, void* stream, double* energy_out,
+                                double* pgs_out) {
+    if (n_inst < 1 || !insts) return fail(SV_ERR_ARG, "sv_batch_p1_scan: no instances");
+    if (n_gamma < 1 || n_beta < 1 || !gammas || !betas) return fail(SV_ERR_ARG, "sv_batch_p1_scan: empty grid");
+    if (!energy_out || !pgs_out) return fail(SV_ERR_ARG, "sv_batch_p1_scan: NULL output");
+    if (!dtype_ok(dtype)) return fail(SV_ERR_ARG, "sv_batch_p1_scan: bad dtype");
+    if ((int64_t)n_gamma * n_beta > (1 << 24)) return fail(SV_ERR_ARG, "sv_batch_p1_scan: grid too large");
+    for (int a = 0; a < n_gamma; a++)
+        if (!std::isfinite(gammas[a])) return fail(SV_ERR_NUMERIC, "sv_batch_p1_scan: gamma %d not finite", a);
+    for (int b = 0; b < n_beta; b++)
+        if (!std::isfinite(betas[b])) return fail(SV_ERR_NUMERIC, "sv_batch_p1_scan: beta %d not finite", b);
+    const int S = batch_lds_bits(
+        (int)dtype, dtype == SV_C64 ? knob_for("batchwide", (int)dtype, 0) : knob_for("batch128", (int)dtype, 0));
+    const int nmax_batch = S + 5;  // direct scan: the high bits of a state fit one thread's 32 registers
+    for (int i = 0; i < n_inst; i++) {
+        if (!insts[i]) return fail(SV_ERR_ARG, "sv_batch_p1_scan: instance %d is NULL", i);
+        if (insts[i]->n > nmax_batch)
+            return fail(SV_ERR_UNSUPPORTED, "sv_batch_p1_scan: instance %d has n=%d > %d", i, insts[i]->n, nmax_batch);
+    }
+    const size_t pts = (size_t)n_gamma * n_beta;
+    std::vector<int> grid, rest;
+    const bool spheres = knob_for("batchsphere", (int)dtype, 0) != 0;
+    for (int i = 0; i < n_inst; i++) (spheres && scan_by_spheres(insts[i]) ? grid : rest).push_back(i);
+    if (!grid.empty()) {
+        std::vector<char> done(grid.size(), 0);
+        hipEvent_t ev0;
+        const bool prof = prof_begin((hipStream_t)stream, &ev0);
+        const int rc = sphere_scan(grid, insts, n_gamma, gammas, n_beta, betas, (hipStream_t)stream, energy_out, pgs_out,
+                                   done);
+        if (prof) prof_end((hipStream_t)stream, ev0, std::string("batch_") + (dtype == SV_C128 ? "c128" : "c64"), 0.0);
+        if (rc) return rc;
+        for (size_t k = 0; k < grid.size(); k++)
+            if (!done[k]) rest.push_back(grid[k]);
+    }
+    if (rest.empty()) return SV_OK;
+    if ((int)rest.size() == n_inst)
+        return direct_scan(n_inst, insts, n_gamma, gammas, n_beta, betas, dtype, stream, energy_out, pgs_out);
+    std::vector<sv_ising> sub;
+    for (int i : rest) sub.push_back(insts[i]);
+    std::vector<double> en(sub.size() * pts), pg(sub.size() * pts);
+    const int rc = direct_scan((int)sub.size(), sub.data(), n_gamma, gammas, n_beta, betas, dtype, stream, en.data(),
+                               pg.data());
+    if (rc) return rc;
+    for (size_t k = 0; k < rest.size(); k++) {
+        memcpy(energy_out + (size_t)rest[k] * pts, en.data() + k * pts, pts * sizeof(double));
+        memcpy(pgs_out + (size_t)rest[k] * pts, pg.data() + k * pts, pts * sizeof(double));
+    }
+    return SV_OK;
+}

@@ -342,6 +342,45 @@ int batch_lds_bits(int dtype, int wide);  // log2 of the LDS-resident state of a
 int batch_lut_cap(int dtype, int wide);   // phase-table entries of a batch variant
 int batch_slice_bits(int dtype, int n);   // log2 of the slice of an n-qubit state on the sliced path
 
+// ---------------------------------------------------------------- landscape scan by spheres
+// sv_scan.hip: the p = 1 scan of instances with energies on a grid Z / q.
+constexpr int kScanMaxN = 19;
+constexpr size_t kScanMaxLds = 64 << 10;  // histogram (n + 1) x levels x 4 B of one ground state
+struct ScanInst {
+    int32_t n, m;
+    int32_t hoff, coff;     // offsets into hq, and cq in triples
+    uint64_t xoff;          // offset of the instance's table indices
+    int32_t lo, q;          // q E(z) = lo + index
+    int32_t zcap;           // ground states listed at most
+    int32_t out;            // index of the instance in the outputs
+    int64_t zoff;           // offset of its ground states
+};
+struct ScanArgs {
+    const ScanInst* inst;
+    const int32_t* hq;      // q h
+    const int32_t* cq;      // (i, j, q J)
+    uint16_t* x;            // table indices q E(z) - lo
+    int32_t* stat;          // per instance: smallest and largest index, number of ground states
+    uint32_t* z;            // ground states
+    double* coef;           // [inst][gamma][3]: A, B, C
+    double2* amps;          // [unit][gamma of the launch][kScanMaxN + 1] sphere sums
+    const int32_t* uinst;   // unit (a ground state) -> instance
+    const int64_t* uoff;    // instance -> its first unit
+    const int32_t* oinst;   // instances that have units, in unit order
+    const double* gammas;
+    const double* betas;
+    double* out_e;
+    double* out_p;
+    int64_t u0, ucount;     // units of this launch
+    int64_t g0;             // gammas of this launch: g0 .. g0 + gc - 1
+    int32_t gc, ng, nb;
+    uint32_t bpi;           // k_scan_index: workgroups per instance
+    uint32_t gpb;           // k_scan_coef: workgroups per instance
+    uint32_t o0;            // first entry of oinst of this launch
+};
+int launch_scan_tables(const ScanArgs& a, int ninst, void* stream);
+int launch_scan_points(const ScanArgs& a, int nout, size_t lds, void* stream);
+
 // ---------------------------------------------------------------- fixed scratch
 // Device region that a call which may not allocate uses instead of the state's
 // work buffers: reduction partials, phase tables and the result array.

@@ -167,6 +167,7 @@ def main(argv=None):
         insts = I.batch_instances(2048)
         Hb = [sv.Ising.from_instance(x) for x in insts]
         gb, bb = I.batch_grid()
+        sv.tune_set("batchsphere", 0)  # the knobs are those of the direct scan
         for dtype in args.dtype:
             best, t, trace = coordinate_descent(
                 sv, BATCH[dtype], lambda: _timer(lambda: sv.batch_p1_scan(Hb, gb, bb, dtype=dtype), args.reps), log,
@@ -176,6 +177,7 @@ def main(argv=None):
             report[f"{dtype} batch"] = {"best": best, "ms": t * 1e3, "trace": trace}
             for k, v in defaults.items():
                 sv.tune_set(k, v)
+        sv.tune_set("batchsphere", 1)
     Path(args.out).write_text("\n".join(lines) + "\n")
     Path(str(args.out) + ".json").write_text(json.dumps(report, indent=1))
     log(f"[tune] wrote {args.out}")

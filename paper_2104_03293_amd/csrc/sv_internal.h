@@ -232,6 +232,26 @@ struct StreamArgs {
 int launch_stream(int dtype, void* p, const StreamArgs& a, void* stream);
 int launch_ground_finish(const GroundArgs& a, double* out_e, uint64_t* out_cnt,
                          uint64_t* out_arg, void* stream);
+// ---------------------------------------------------------------- ground states
+// Enumeration over an independent set (sv_ground.hip); energies in units of 1/q.
+// A term (mask, c) of a setting x of the r other spins is c (-1)^{parity(x & mask)}.
+constexpr int kMaxGroundTerms = 640;
+constexpr int kGroundBlocks = 2048;
+struct GroundSetArgs {
+    const int2* terms;      // [0, first[0]): E of the rest; [first[i], first[i + 1]): F of set spin i
+    int32_t nterms;
+    int32_t r, k;
+    int32_t e0;
+    int32_t h[34];          // field of set spin i
+    int32_t first[35];
+    uint8_t rest[34];       // bit b of x -> qubit
+    uint8_t spin[34];       // set spin i -> qubit
+    int32_t* part_e;        // per workgroup
+    unsigned long long* part_c;  // count, first index
+    unsigned long long* out;     // energy, count, first index
+};
+int launch_ground_sets(const GroundSetArgs& a, int nblocks, void* stream);
+
 // ---------------------------------------------------------------- small tiles
 // Tile programs of states that the large tiles cannot spread over the chip
 // (sv_tile.hip).  Layout j of a tile holds tile bits [lb, lb + 4) in registers,

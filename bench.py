@@ -499,7 +499,7 @@ def committed_traffic(dtype: str, n: int, p: int):
     if not f.exists():
         return None
     text = f.read_text()
-    src = ROOT / "paper_2104_03293_amd" / "csrc" / "sv_kernels.hip"
+    src = ROOT / "paper_2104_03293_amd" / "csrc" / "sv_pass.h"
     sha = hashlib.sha256(src.read_bytes()).hexdigest()
     m = re.search(r"kernel source sha256: ([0-9a-f]{64})", text)
     t = re.search(r"traffic_bytes_per_launch: ([0-9.eE+]+)", text)

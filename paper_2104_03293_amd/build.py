@@ -24,7 +24,8 @@ LIB_SAN = HERE / "libsv_san.so"
 HOST_SRCS = [CSRC / "sv_host_core.cpp", CSRC / "sv_plan.cpp", CSRC / "sv_tile_host.cpp", CSRC / "sv_api.cpp", CSRC / "sv_batch.cpp",
              CSRC / "sv_noalloc.hip"]
 # gfx950 kernels
-KERNEL_SRCS = [CSRC / "sv_kernels.hip", CSRC / "sv_tile.hip", CSRC / "sv_scan.hip",
+KERNEL_SRCS = [CSRC / "sv_kernels.hip", CSRC / "sv_pass_c128.hip", CSRC / "sv_pass_c64.hip", CSRC / "sv_pass_pair.hip",
+               CSRC / "sv_tile.hip", CSRC / "sv_scan.hip",
                CSRC / "sv_ground.hip"]
 CLANG_DIR = Path(os.environ.get("SV_CLANG_DIR", "/opt/rocm/llvm/bin"))
 

@@ -97,13 +97,36 @@ struct TileGeom {
     }
 };
 
-// Wave-level sum of a per-lane value (fixed butterfly order), added by lane 0
-// to this wave's row of the per-workgroup reduction array.
-template <int NS>
-__device__ __forceinline__ void wave_add(double (*s_red)[NS], int slot, double v) {
+// Thread part of E for layout L: returns e0 = E at register index 0 and the
+// register-bit fields f[k], so that E(r) = e0 + sum_{k: r_k = 1} 2 f[k] + Q[r].
+// s_g holds the tile's g_l (l < T) and E_fixed (entry kTF - 1).  The couplings
+// inside the tile that involve thread bits come from the layout's per-thread
+// table (one coalesced load per row).
+template <int R, int NTB>
+__device__ __forceinline__ double thread_energy(CGeoLayout* L, CGeoBuf* geo, uint32_t t,
+                                                const double* s_g, double (&f)[R]) {
+    constexpr int NT = 1 << NTB;
+    const uint32_t off = L->thr_off;
+    const SV_CONST double* __restrict__ tab = reinterpret_cast<const SV_CONST double*>(geo) + off + t;
+    double eth = s_g[kTF - 1];
+    uint32_t m = L->tmask;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6][slot] += v;
+    for (int j = 0; j < NTB; j++) {
+        const int l = __builtin_ctz(m);
+        m &= m - 1u;
+        const double gl = s_g[l];
+        eth += ((t >> j) & 1u) ? gl : -gl;
+    }
+    if (off != 0) eth += tab[0];
+    const uint32_t rbp = L->rbpack;
+#pragma unroll
+    for (int k = 0; k < R; k++) {
+        double fv = s_g[(rbp >> (4 * k)) & 15u];
+        if (off != 0) fv += tab[(1 + k) * NT];
+        f[k] = fv;
+        eth -= fv;
+    }
+    return eth;
 }
 
 // Value of x in lane r (the same r in every lane), as a scalar.
@@ -112,6 +135,32 @@ __device__ __forceinline__ double lane_value(double x, int r) {
     const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(b & 0xffffffffll), r);
     const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), r);
     return __longlong_as_double(((long long)hi << 32) | (long long)lo);
+}
+
+// Wave sum, the same in every lane: within rows of 16 by DPP moves (lane ^ 1, lane ^ 2, mirrored
+// halves, mirrored row), then the four rows as scalars.  A third of the latency of six
+// cross-lane reads through LDS.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return v + __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v = dpp_add<0xB1>(v);   // quad_perm 1 0 3 2
+    v = dpp_add<0x4E>(v);   // quad_perm 2 3 0 1
+    v = dpp_add<0x141>(v);  // row_half_mirror
+    v = dpp_add<0x140>(v);  // row_mirror
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// Wave-level sum of a per-lane value, added by lane 0 to this wave's row of the
+// per-workgroup reduction array.
+template <int NS>
+__device__ __forceinline__ void wave_add(double (*s_red)[NS], int slot, double v) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6][slot] += v;
 }
 
 __device__ __forceinline__ double2 cmul(double2 x, double2 y) {

@@ -53,7 +53,7 @@ struct Work {
     double* h_res = nullptr;
     size_t res_cap = 0;  // doubles
     bool res_on_host = false;  // the last program wrote its results to h_res itself
-    double* d_spin = nullptr;  // per-tile spin partials [ntiles][kTF]
+    double* d_spin = nullptr;  // per-tile spin partials [kTF][ntiles]
     size_t spin_cap = 0;       // doubles
     double* d_gmat = nullptr;  // general single-qubit layers, kGenBlock doubles per MIX op
     double* h_gmat = nullptr;  // pinned staging copy
@@ -185,6 +185,13 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
 // PT_ZETA's t and -t and store no state; the second's results follow the first's.
 int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, const Plan& plan, bool need_ground,
                      const FixedScratch* fx = nullptr, const void* first_src = nullptr, bool dual = false);
+// Results of a program from its columns of partial sums, in one launch per 256 results.
+int gather_results(sv_state_s* s, const double* part, uint64_t ntiles, double* out,
+                   const std::vector<std::vector<uint32_t>>& segs);
+// Columns (GatherArgs::seg) of <sigma^z_i> of a pass whose spin columns start at col: the tile bit's
+// column, or the norm column (norm) signed by a bit of the tile index.
+void spin_segments(const Geometry& geo, int n, int col, int norm, std::vector<uint32_t>* segs);
+int prepare_passes(sv_state_s* s, sv_ising_s* H, const Program& prog, const Plan& plan);
 int fetch_results(sv_state_s* s, int nres);
 int ensure_work(sv_state_s* s, size_t part_doubles, size_t res_doubles);
 // Pinned staging buffer for nblk matrix blocks of general layers (waits until an earlier

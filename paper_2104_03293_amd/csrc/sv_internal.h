@@ -69,10 +69,10 @@ enum PointFlags : int32_t {
     PT_EFORM = 256      // one-vector passes: slot2 += E |psi|^2
 };
 
-// Per-tile spin partials (PT_SPINZ): kTF doubles per tile, entry l < T =
-// sum over the tile of |psi|^2 s_l, entry kTF - 1 = sum of |psi|^2.
+// Per-tile spin partials (PT_SPINZ): kTF columns, column l < T =
+// sum over the tile of |psi|^2 s_l, column kTF - 1 = sum of |psi|^2.
 struct SpinArgs {
-    const double* part;     // [ntiles][kTF]
+    const double* part;     // [kTF][ntiles]
     uint64_t ntiles;
     int32_t c, lo, g, T, n;
     int32_t qubit[16];      // tile bit -> qubit (-1: phantom)
@@ -150,7 +150,7 @@ struct PassArgs {
     void* psi;
     void* lam;
     const void* src;        // psi is loaded from here when non-null (out-of-place first pass), else from psi
-    double* partials;       // [ntiles][nslots]
+    double* partials;       // [nslots][ntiles]
     const double2* ptab;    // phase tables (k_tables output)
     const GeoBuf* geo;
     const double* tf;       // per-tile field table (passes that evaluate E)
@@ -173,7 +173,7 @@ struct PassArgs {
     int32_t nphase;
     int32_t lut_half;       // L of the phase tables (in units of 1/q), -1 for other real-valued instances
     double lut_q;           // q: table index = q * energy
-    double* spin_part;      // [ntiles][kTF] spin partials (passes with PT_SPINZ)
+    double* spin_part;      // [kTF][ntiles] spin partials (passes with PT_SPINZ)
     const double* gmat;     // general single-qubit layers (passes whose MIX ops carry MIX_GEN), else null
     int32_t gen_real;       // every general layer of the pass is real
     int32_t gen_unit;       // every general layer of the pass is in the unit-diagonal form (MIX_GUNIT)
@@ -212,7 +212,11 @@ struct TfArgs {
 };
 
 // Launchers (sv_kernels.hip).  Return hipError_t as int.
-int launch_pass(int dtype, int nv, int T, const PassArgs& a, void* stream);
+int launch_pass(int dtype, int nv, int T, int R, const PassArgs& a, void* stream);
+int launch_pass_c128(int T, const PassArgs& a, void* stream);  // sv_pass_*.hip
+int launch_pass_c128_pair(const PassArgs& a, void* stream);
+int launch_pass_c64(int T, const PassArgs& a, void* stream);
+int launch_pass_c64_pair(int T, int R, const PassArgs& a, void* stream);
 int launch_tile_fields(const TfArgs& a, void* stream);
 int launch_tables(const TableJob* jobs, int njobs, double2* out, void* stream);
 int launch_spin_reduce(const SpinArgs& a, void* stream);

@@ -236,7 +236,10 @@ std::vector<Geometry> plan_groups(int n, sv_dtype dt, int nv, bool grad, bool ge
     int lo = T;
     for (int i = 0; i < ng; i++) {
         int g = largest_first ? std::min(gmax, n - lo) : rest / ng + (i < rest % ng ? 1 : 0);
-        out.push_back(make_geometry(n, T, R, T - g, lo, g, G, dpp, nv == 1));
+        // 13-bit complex64 two-vector tiles: 32 amplitudes per thread and vector for the strided
+        // groups (one exchange fewer per mixer), 16 for the contiguous one
+        const int Rg = dt == SV_C64 && nv == 2 && T == 13 ? 5 : R;
+        out.push_back(make_geometry(n, T, Rg, T - g, lo, g, G, dpp, nv == 1));
         lo += g;
     }
     return out;
@@ -853,9 +856,18 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
         emin = H->emin;
         etol = ground_tol(H);
     }
-    size_t part_need = 1;
+    // Reductions of states with few tiles are left to one gather launch at the end (columns of all
+    // passes kept): two launches after every pass cost 9 us and a spin sum 5 us, as much as 10-25 % of
+    // a pass at n = 23.  With more tiles (one workgroup per result would be slow) they follow the pass.
+    const uint64_t nt0 = plan.by_nv[1][0].ntiles;
+    size_t ncol = 0;
+    for (const Pass& p : prog.passes) ncol += p.slot_dst.size() + (p.spin_res >= 0 ? kTF : 0);
+    bool defer = prog.nres > 0 && nt0 <= 8192 && ncol < (size_t(1) << 23) && ncol * nt0 <= (size_t(8) << 20);
+    for (const Pass& p : prog.passes) defer = defer && plan.by_nv[p.nv][p.group].ntiles == nt0;
+    std::vector<std::vector<uint32_t>> segs(defer ? prog.nres : 0);
+    size_t part_need = defer ? ncol * nt0 : 1;
     for (const Pass& p : prog.passes)
-        part_need = std::max(part_need, (size_t)plan.by_nv[p.nv][p.group].ntiles * std::max<size_t>(1, p.slot_dst.size()));
+        if (!defer) part_need = std::max(part_need, (size_t)plan.by_nv[p.nv][p.group].ntiles * std::max<size_t>(1, p.slot_dst.size()));
     int rc = SV_OK;
     // the slot reduction's first stage follows the partials
     const size_t stage_off = part_need;
@@ -879,7 +891,7 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
     double* const d_part = fx ? fx->part : s->w.d_part;
     size_t spin_need = 0;
     for (const Pass& p : prog.passes)
-        if (p.spin_res >= 0) spin_need = std::max(spin_need, (size_t)plan.by_nv[p.nv][p.group].ntiles * kTF);
+        if (p.spin_res >= 0 && !defer) spin_need = std::max(spin_need, (size_t)plan.by_nv[p.nv][p.group].ntiles * kTF);
     if (spin_need > s->w.spin_cap) {
         if (s->w.d_spin) (void)hipFree(s->w.d_spin);
         s->w.d_spin = nullptr;
@@ -887,7 +899,7 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
         HIPCHECK(hipMalloc(&s->w.d_spin, spin_need * sizeof(double)));
         s->w.spin_cap = spin_need;
     }
-    if (prog.nres > 0 && !fx) {
+    if (prog.nres > 0 && !fx && !defer) {
         hipError_t e = hipMemsetAsync(s->w.d_res, 0, prog.nres * sizeof(double), s->stream);
         if (e != hipSuccess) {
             s->failed = true;
@@ -1018,6 +1030,7 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
     const int persist = knob_for("persist", (int)s->dt, s->n);
     const int stagger = knob_for("stagger", (int)s->dt, s->n);
     const int ncu = persist > 0 ? device_cu_count(s->device) : 0;
+    int col = 0;  // first column of the pass (deferred reductions)
     for (size_t pi = 0; pi < prog.passes.size(); pi++) {
         const Pass& p = prog.passes[pi];
         const Geometry& geo = plan.by_nv[p.nv][p.group];
@@ -1064,6 +1077,15 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
         a.lut_half = lut_half;
         a.lut_q = H && H->qden > 0 ? (double)H->qden : 1.0;
         a.spin_part = p.spin_res >= 0 ? s->w.d_spin : nullptr;
+        if (defer) {
+            a.partials = d_part + (size_t)col * nt0;
+            for (int d : p.slot_dst) segs[d].push_back((uint32_t)col++ | 255u << 24);
+            if (p.spin_res >= 0) {
+                a.spin_part = d_part + (size_t)col * nt0;
+                spin_segments(geo, s->n, col, col + kTF - 1, &segs[p.spin_res]);
+                col += kTF;
+            }
+        }
         for (int q = 0; q < a.nphase; q++) {
             a.qph_off[q] = offs[pi][q].first;
             a.lut_off[q] = offs[pi][q].second;
@@ -1100,7 +1122,7 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
         }
         hipEvent_t ev0;
         const bool prof = !fx && prof_begin(s->stream, &ev0);
-        int e = take_injected_failure() ? (int)hipErrorLaunchFailure : launch_pass((int)s->dt, p.nv, geo.T, a, s->stream);
+        int e = take_injected_failure() ? (int)hipErrorLaunchFailure : launch_pass((int)s->dt, p.nv, geo.T, geo.R, a, s->stream);
         if (prof) {
             const int nrd = (p.load & 4) ? 0 : __builtin_popcount(p.load & 3);
             const int nwr = __builtin_popcount(p.store & 3);
@@ -1116,6 +1138,7 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
             s->failed = true;
             return fail(SV_ERR_HIP, "pass launch failed: %s", hipGetErrorString((hipError_t)e));
         }
+        if (defer) continue;
         if (p.spin_res >= 0) {
             SpinArgs sa;
             memset(&sa, 0, sizeof(sa));
@@ -1142,6 +1165,31 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
                 return fail(SV_ERR_HIP, "reduce launch failed: %s", hipGetErrorString((hipError_t)e));
             }
         }
+    }
+    if (!defer) return SV_OK;
+    s->w.res_on_host = !fx;
+    return gather_results(s, d_part, nt0, fx ? fx->out : s->w.h_res, segs);
+}
+
+// Builds the instance's tables for the passes of a program (and records small-tile passes) as a run
+// of it would: a program that leaves identity factors out still prepares the calls that may not
+// build tables for those that have them.
+int prepare_passes(sv_state_s* s, sv_ising_s* H, const Program& prog, const Plan& plan) {
+    for (const Pass& p : prog.passes) {
+        bool point = false;
+        for (const Op& op : p.ops) point = point || op.kind == OP_POINT;
+        if (plan.tile) {
+            std::lock_guard<std::mutex> g(H->mu);
+            H->tile_seen.insert(std::make_tuple((int)s->dt, plan.by_nv[1][0].T, p.group, point));
+            if (point) H->tile_seen.insert(std::make_tuple((int)s->dt, plan.by_nv[1][0].T, p.group, false));
+            continue;
+        }
+        const Geometry& geo = plan.by_nv[p.nv][p.group];
+        GeoBuf* gb = nullptr;
+        int rc = get_geobuf(geo, H, s->dt, &gb);
+        const double* tf = nullptr;
+        if (!rc && point) rc = get_tf(H, geo, gb, s->stream, &tf);
+        if (rc) return rc;
     }
     return SV_OK;
 }

@@ -90,24 +90,6 @@ __device__ __forceinline__ X mul_im(X ar, X ai, X br, X bi) {
     return fma(ar, bi, ai * br);
 }
 
-// Wave sum, the same in every lane: within rows of 16 by DPP moves (lane ^ 1, lane ^ 2, mirrored
-// halves, mirrored row), then the four rows as scalars.  A third of the latency of six
-// cross-lane reads through LDS.
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return v + __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-__device__ __forceinline__ double wave_sum(double v) {
-    v = dpp_add<0xB1>(v);   // quad_perm 1 0 3 2
-    v = dpp_add<0x4E>(v);   // quad_perm 2 3 0 1
-    v = dpp_add<0x141>(v);  // row_half_mirror
-    v = dpp_add<0x140>(v);  // row_mirror
-    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
-}
-
 // Workgroup sums of N per-thread values in a fixed order, handed to
 // put(i, sum) by thread i (any thread for one wave).
 template <int N, int NW, typename Put>
@@ -601,10 +583,10 @@ int launch_tile(int dtype, int nv, int T, const TileArgs& a, void* stream) {
     return a.resident ? run_tile_feat<float, double>(T, a, st) : run_tile_feat<float, float>(T, a, st);
 }
 
-// Second stage of the reductions of a tile program, one workgroup per result:
-// result i sums its columns of the partial sums ([column][tile]) in a fixed
-// order; a column may be signed by one bit of the tile index (spin
-// expectations of qubits outside the tile).
+// Second stage of the reductions of a program, one workgroup per result: result
+// i sums its columns of the partial sums ([column][tile]) in a
+// fixed order; a column may be signed by one bit of the tile index
+// (spin expectations of qubits outside the tile).
 __global__ void __launch_bounds__(256) k_gather(const GatherArgs a) {
     __shared__ double sh[4];
     const SV_CONST GatherArgs* ka = (const SV_CONST GatherArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -615,6 +597,7 @@ __global__ void __launch_bounds__(256) k_gather(const GatherArgs a) {
         const uint32_t seg = ka->seg[s];
         const double* __restrict__ col = a.part + (uint64_t)(seg & 0xffffffu) * a.ntiles;
         const uint32_t sb = seg >> 24;  // 255: unsigned
+#pragma unroll 4
         for (uint32_t w = t; w < a.ntiles; w += 256) {
             const double x = col[w];
             v += (sb != 255u && !((w >> sb) & 1u)) ? -x : x;

@@ -122,14 +122,7 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
         if (p.spin_res >= 0) {
             spin = single ? p.spin_res : ncol;
             if (!single) {
-                const Geometry& geo = groups[p.group];
-                for (int i = 0; i < s->n; i++) {
-                    const bool in = i < geo.c || (i >= geo.lo && i < geo.lo + geo.g);
-                    const int l = i < geo.c ? i : geo.c + (i - geo.lo);  // tile bit
-                    const int w = i < geo.lo ? i - geo.c : i - geo.g - geo.c;  // bit of the tile index
-                    segs[p.spin_res + i].push_back(in ? (uint32_t)(ncol + l) | 255u << 24
-                                                      : (uint32_t)(ncol + T) | (uint32_t)w << 24);
-                }
+                spin_segments(groups[p.group], s->n, ncol, ncol + T, &segs[p.spin_res]);
                 ncol += T + 1;
             }
         }
@@ -298,13 +291,27 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
         }
     }
     if (single || prog.nres == 0) return SV_OK;
-    for (int r0 = 0; r0 < prog.nres;) {
+    return gather_results(s, part, ntiles, out, segs);
+}
+
+void spin_segments(const Geometry& geo, int n, int col, int norm, std::vector<uint32_t>* segs) {
+    for (int i = 0; i < n; i++) {
+        const bool in = i < geo.c || (i >= geo.lo && i < geo.lo + geo.g);
+        const int l = i < geo.c ? i : geo.c + (i - geo.lo);        // tile bit
+        const int w = i < geo.lo ? i - geo.c : i - geo.g - geo.c;  // bit of the tile index
+        segs[i].push_back(in ? (uint32_t)(col + l) | 255u << 24 : (uint32_t)norm | (uint32_t)w << 24);
+    }
+}
+
+int gather_results(sv_state_s* s, const double* part, uint64_t ntiles, double* out,
+                   const std::vector<std::vector<uint32_t>>& segs) {
+    for (size_t r0 = 0; r0 < segs.size();) {
         GatherArgs ga;
         ga.part = part;
         ga.out = out + r0;
         ga.ntiles = (uint32_t)ntiles;
         int n = 0, k = 0;
-        while (r0 + n < prog.nres && n < 256 && k + (int)segs[r0 + n].size() <= 768) {
+        while (r0 + n < segs.size() && n < 256 && k + (int)segs[r0 + n].size() <= 768) {
             ga.first[n] = (uint16_t)k;
             for (uint32_t sg : segs[r0 + n]) ga.seg[k++] = sg;
             n++;

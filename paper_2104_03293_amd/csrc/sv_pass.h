@@ -928,13 +928,26 @@ static int run_pass(const PassArgs& a, void* stream) {
         // the register pressure below the two-workgroups-per-CU limit
         // (nontemporal variants for passes over long contiguous runs)
         if constexpr (NV == 1) {
-            if (a.spin_part) {  // passes that also sum the spin expectations (more registers)
+            if (a.spin_part) {
+                // passes that also sum the spin expectations: straight-line walks fit the plain
+                // kernels' register budget (the layout loop spills 200-280 B per thread in it; with
+                // half the workgroups per CU instead, the n = 23 complex64 passes took 61-73 us, now 37-41)
                 constexpr int SMB = MINB > 2 ? 2 : MINB;
+                const bool nts = a.nt == 3;
                 if (a.nlayouts == 1)
-                    hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, SMB, false, true, 1, 0, false, true>), grid, block,
+                    hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, MINB, false, true, 1, 0, false, true>), grid, block,
+                                       0, st, a);
+                else if (a.nlayouts == 2 && nts)
+                    hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, MINB, false, true, 2, 3, false, true>), grid, block,
                                        0, st, a);
                 else if (a.nlayouts == 2)
-                    hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, SMB, false, true, 2, 0, false, true>), grid, block,
+                    hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, MINB, false, true, 2, 0, false, true>), grid, block,
+                                       0, st, a);
+                else if (a.nlayouts == 3 && nts)
+                    hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, MINB, false, true, 3, 3, false, true>), grid, block,
+                                       0, st, a);
+                else if (a.nlayouts == 3)
+                    hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, MINB, false, true, 3, 0, false, true>), grid, block,
                                        0, st, a);
                 else
                     hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, SMB, false, true, 0, 0, false, true>), grid, block,

@@ -163,6 +163,37 @@ __device__ __forceinline__ void wave_add(double (*s_red)[NS], int slot, double v
     if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6][slot] += v;
 }
 
+// (cos x, -sin x) for |x| <= kTileMaxAngle (the host sends programs with larger
+// phase angles to kernels that call the library function).  Two-term reduction by pi/2 with fused
+// multiply-adds (x - k hi(pi/2) is exact for |x| <= 2^16: both are multiples of
+// 2^-52 and the difference is below 1) and Taylor polynomials on [-pi/4, pi/4]
+// (first dropped terms: 8e-20 for the sine, 2e-18 for the cosine).
+__device__ __forceinline__ double2 cis_neg(double x) {
+    const double k = rint(x * 0.63661977236758134);
+    const double r = fma(-k, 6.123233995736766e-17, fma(-k, 1.5707963267948966, x));
+    const double z = r * r;
+    double s = 1.0 / 355687428096000.0, c = 1.0 / 20922789888000.0;
+    s = fma(s, z, -1.0 / 1307674368000.0);
+    c = fma(c, z, -1.0 / 87178291200.0);
+    s = fma(s, z, 1.0 / 6227020800.0);
+    c = fma(c, z, 1.0 / 479001600.0);
+    s = fma(s, z, -1.0 / 39916800.0);
+    c = fma(c, z, -1.0 / 3628800.0);
+    s = fma(s, z, 1.0 / 362880.0);
+    c = fma(c, z, 1.0 / 40320.0);
+    s = fma(s, z, -1.0 / 5040.0);
+    c = fma(c, z, -1.0 / 720.0);
+    s = fma(s, z, 1.0 / 120.0);
+    c = fma(c, z, 1.0 / 24.0);
+    s = fma(s, z, -1.0 / 6.0);
+    s = fma(s * z, r, r);
+    const double h = 0.5 * z, w = 1.0 - h;  // 1 - z/2 + z^2 c with the rounding error of 1 - z/2 put back
+    c = w + fma(z * z, c, (1.0 - w) - h);
+    const int q = (int)k;
+    const double cs = (q & 1) ? s : c, sn = (q & 1) ? c : s;
+    return make_double2(((q + 1) & 2) ? -cs : cs, (q & 2) ? sn : -sn);
+}
+
 __device__ __forceinline__ double2 cmul(double2 x, double2 y) {
     return make_double2(x.x * y.x - x.y * y.y, x.x * y.y + x.y * y.x);
 }

@@ -172,6 +172,7 @@ struct PassArgs {
                             // walks K / 8 contiguous stretches of the tiles; 0: tile = b
     int32_t nphase;
     int32_t lut_half;       // L of the phase tables (in units of 1/q), -1 for other real-valued instances
+    int32_t libm;           // real-valued instance with phase angles beyond kTileMaxAngle: library sincos
     double lut_q;           // q: table index = q * energy
     double* spin_part;      // [kTF][ntiles] spin partials (passes with PT_SPINZ)
     const double* gmat;     // general single-qubit layers (passes whose MIX ops carry MIX_GEN), else null

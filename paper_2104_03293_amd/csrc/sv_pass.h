@@ -333,7 +333,7 @@ __device__ __forceinline__ int tmask_bit(uint32_t tmask, int j) {
 
 // KC > 0: the pass geometry has exactly KC layouts (compile time, straight-line
 // layout walks); KC == 0: generic kernel with a runtime layout count (used for
-// states smaller than one tile and for real-valued instances).
+// states smaller than one tile and for phase angles that need the library's sincos).
 template <typename Real, int T, int R, int NV, int NS, int MINB, bool PH, bool INTE, int KC, int NTM = 0,
           bool PERSIST = false, bool SPZ = PH, int GEN = 0, int QFM = 0>
 __global__ void __launch_bounds__(1 << (T - R), MINB) k_pass(const PassArgs a) {
@@ -701,7 +701,7 @@ __global__ void __launch_bounds__(1 << (T - R), MINB) k_pass(const PassArgs a) {
                     const SV_CONST double* __restrict__ qph = (const SV_CONST double*)(a.ptab + a.qph_off[op.qidx]);
                     double2 gk[R];
                     double2 run;
-                    if constexpr (INTE) {
+                    if (INTE && a.lut_half >= 0) {
                         // energies on the grid Z / q: factors from the table exp(-i gamma m / q)
                         const SV_CONST double* __restrict__ lut =
                             (const SV_CONST double*)(a.ptab + a.lut_off[op.qidx] + a.lut_half);
@@ -713,20 +713,34 @@ __global__ void __launch_bounds__(1 << (T - R), MINB) k_pass(const PassArgs a) {
                         }
                         run = ctab(lut, min(max((int)(e0 * a.lut_q), -Lh), Lh));
                     } else {
-                        // One sincos at a time: the fma(0, previous sine, x) link (exact
-                        // for finite values) keeps the scheduler from interleaving the
-                        // R + 1 evaluations, which would exhaust the register file.
+                        // One evaluation at a time: the fma(0, previous sine, x) link (exact
+                        // for finite values) keeps the scheduler from interleaving the R + 1 of
+                        // them, which would exhaust the register file.  INTE kernels take other
+                        // energies too, up to kTileMaxAngle (270 instructions per thread and phase,
+                        // within the registers of two workgroups per CU: n = 23 complex128, p = 8 920 ->
+                        // 600 us, the rate of integer couplings); the others call the library.
                         double link = 0.0;
 #pragma unroll
                         for (int k = 0; k < R; k++) {
-                            double sn, cs;
-                            sincos(fma(0.0, link, 2.0 * gam * f[k]), &sn, &cs);
-                            gk[k] = make_double2(cs, -sn);
-                            link = sn;
+                            const double x = fma(0.0, link, 2.0 * gam * f[k]);
+                            if constexpr (INTE) {
+                                gk[k] = cis_neg(x);
+                                link = gk[k].y;
+                            } else {
+                                double sn, cs;
+                                sincos(x, &sn, &cs);
+                                gk[k] = make_double2(cs, -sn);
+                                link = sn;
+                            }
                         }
-                        double sn, cs;
-                        sincos(fma(0.0, link, gam * e0), &sn, &cs);
-                        run = make_double2(cs, -sn);
+                        const double x = fma(0.0, link, gam * e0);
+                        if constexpr (INTE) {
+                            run = cis_neg(x);
+                        } else {
+                            double sn, cs;
+                            sincos(x, &sn, &cs);
+                            run = make_double2(cs, -sn);
+                        }
                     }
                     // the phase has modulus one: the pending scales stay pending (they are
                     // applied at the store)
@@ -849,10 +863,10 @@ static void launch_gen_fast(const PassArgs& a, dim3 grid, dim3 block, hipStream_
 template <typename Real, int T, int R, int NS, int MINB, int QFM>
 static int launch_qf(const PassArgs& a, bool fast, dim3 grid, dim3 block, hipStream_t st) {
     constexpr int PMB = MINB > 2 ? 2 : MINB;
-    if (!fast && a.lut_half >= 0) {  // states smaller than one tile
+    if (!fast && !a.libm) {  // states smaller than one tile
         hipLaunchKernelGGL((k_pass<Real, T, R, 1, NS, PMB, true, true, 0, 0, false, false, 0, QFM>), grid, block, 0, st,
                            a);
-    } else if (!fast) {  // real-valued instances: FP64 sincos
+    } else if (!fast) {  // phase angles beyond kTileMaxAngle off the energy grid: library sincos
         hipLaunchKernelGGL((k_pass<Real, T, R, 1, NS, 1, true, false, 0, 0, false, false, 0, QFM>), grid, block, 0, st,
                            a);
     } else if (a.nlayouts == 1) {
@@ -888,11 +902,11 @@ template <typename Real, int T, int R, int NV, int NS, int MINB>
 static int run_pass(const PassArgs& a, void* stream) {
     // persistent grids exist for the one-vector fast paths with >= 2 layouts
     const bool pers = NV == 1 && a.grid > 0 && (uint64_t)a.grid < a.ntiles && a.nlayouts >= 2 && a.phantom == 0 &&
-                      (a.lut_half >= 0 || a.nphase == 0);
+                      !a.libm;
     const unsigned nwg = pers ? (unsigned)a.grid : (unsigned)a.ntiles;
     const dim3 grid(nwg), block(1 << (T - R));
     hipStream_t st = (hipStream_t)stream;
-    const bool fast = a.phantom == 0 && (a.lut_half >= 0 || a.nphase == 0);
+    const bool fast = a.phantom == 0 && !a.libm;
     // general-layer kernels exist for 13-bit complex128 and 14-bit complex64 tiles
     if constexpr (NV == 1 && ((sizeof(Real) == 8 && T == 13) || (sizeof(Real) == 4 && T == 14))) {
         if (a.gmat) {  // general single-qubit layers (real matrices: half the arithmetic)
@@ -995,13 +1009,13 @@ static int run_pass(const PassArgs& a, void* stream) {
             hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, MINB, false, true, 0, 3>), grid, block, 0, st, a);
         else
             hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, MINB, false, true, 0>), grid, block, 0, st, a);
-    } else if (a.lut_half >= 0) {
+    } else if (!a.libm) {
         // states smaller than one tile (phantom bits): correctness over occupancy
         constexpr int PMB = MINB > 2 ? 2 : MINB;
         hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, PMB, true, true, 0>), grid, block, 0, st, a);
     } else {
-        // real-valued instances: FP64 sincos per thread needs more registers;
-        // one workgroup per CU lets the compiler keep them in the AGPR half
+        // large phase angles off the energy grid: the library's sincos needs more registers;
+        // one workgroup per CU leaves it the whole file
         hipLaunchKernelGGL((k_pass<Real, T, R, NV, NS, 1, true, false, 0>), grid, block, 0, st, a);
     }
     return (int)hipGetLastError();

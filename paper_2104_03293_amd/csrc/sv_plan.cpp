@@ -1075,6 +1075,8 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
         a.nphase = (int)p.phase.size();
         a.ptab = d_tab;
         a.lut_half = lut_half;
+        for (const auto& ph : p.phase)
+            if (lut_half < 0 && 4.0 * std::fabs(ph.second) * H->scale > kTileMaxAngle) a.libm = 1;
         a.lut_q = H && H->qden > 0 ? (double)H->qden : 1.0;
         a.spin_part = p.spin_res >= 0 ? s->w.d_spin : nullptr;
         if (defer) {

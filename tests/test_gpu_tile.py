@@ -101,3 +101,19 @@ def test_phase_angles_beyond_the_small_tiles(sv, orc, n):
     for gam in (1.0e3, 1.0e6):
         sv.qaoa_forward(s, H, [gam], [0.4])
         assert np.max(np.abs(s.to_numpy() - orc.qaoa_state(inst, [gam], [0.4]))) <= 1e-9  # angle rounding: eps * 1e7
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("gam", [300.0, 4.0e4])
+def test_real_couplings_on_the_large_tiles(sv, orc, gam, dtype):
+    """Real-valued couplings on full large tiles, with phase angles inside and beyond the range of the
+    in-place phase factors (beyond it the library's sincos kernels run)."""
+    n = 22
+    inst = I.random_real(n, 2 * n, 7)
+    H = sv.Ising.from_instance(inst)
+    s, lam = sv.State(n, dtype), sv.State(n, dtype)
+    sv.qaoa_forward(s, H, [gam, 0.3], [0.4, -0.2])
+    ref = orc.qaoa_state(inst, [gam, 0.3], [0.4, -0.2])
+    # the angle itself is known to eps * gamma * sum(|h| + |J|); amplitudes are about 2^-11
+    tol = AMP_TOL[dtype] + 2.0 ** -50 * gam * orc.coeff_scale(inst)
+    assert np.max(np.abs(s.to_numpy() - ref)) <= tol

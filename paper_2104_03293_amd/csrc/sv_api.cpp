@@ -536,7 +536,7 @@ extern "C" int sv_gate_layers(sv_state s, int nlayers, const double* U) {
         if (!std::isfinite(U[i]))
             return fail(SV_ERR_NUMERIC, "sv_gate_layers: non-finite entry in layer %d, qubit %d", (int)(i / 8 / s->n),
                         (int)(i / 8 % s->n));
-    Plan plan = make_plan(s->n, s->dt, false, true);
+    Plan plan = make_plan(s->n, s->dt, false, true, true, false);
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)s->dt, s->n);
     const int ng = (int)order.size();
     // Gates on different qubits commute, so each tile group takes up to four
@@ -685,6 +685,7 @@ extern "C" int sv_qsds_run(sv_state s, sv_ising H, int steps, double tau, const 
     prog.layers = layers.data();
     prog.nq = n;
     rc = run_program(s, nullptr, H, prog, plan, want);
+    if (!rc) rc = prepare_energy_passes(s, H);
     if (rc || nres == 0) return rc;
     rc = fetch_results(s, nres);
     if (rc) return rc;
@@ -804,7 +805,7 @@ static int grad_resident(sv_state_s* psi, sv_ising_s* H, int p, const double* ga
 static int grad_zeta(sv_state_s* psi, sv_state_s* lam, sv_ising_s* H, int p, const double* gamma,
                      const double* beta, int psi_is_forward, double* energy, double* p_gs, double* dgamma,
                      double* dbeta) {
-    Plan plan = make_plan(psi->n, psi->dt, false, false, tile_angles(H, p, gamma));
+    Plan plan = make_plan(psi->n, psi->dt, false, true, tile_angles(H, p, gamma), false);
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)psi->dt, psi->n);
     const bool fuse = knob_for("fuse", (int)psi->dt, psi->n) != 0;
     const double t = zeta_scale(H);
@@ -838,6 +839,8 @@ static int grad_zeta(sv_state_s* psi, sv_state_s* lam, sv_ising_s* H, int p, con
     rc = fetch_results(lam, 2 * p + 3);
     if (rc) return rc;
     rc = fetch_results(psi, 2 * p);
+    if (rc) return rc;
+    rc = prepare_energy_passes(psi, H);
     if (rc) return rc;
     if (energy) *energy = lam->w.h_res[2 * p + 1];
     if (p_gs) *p_gs = lam->w.h_res[2 * p + 2];
@@ -1015,6 +1018,19 @@ extern "C" int sv_schedule_second_order(int p, double tau, const double* A, cons
 }
 
 // ============================================================================ describe
+static std::string geometry_json(const Geometry& g) {
+    std::string js = "{\"T\":" + std::to_string(g.T) + ",\"R\":" + std::to_string(g.R) + ",\"c\":" + std::to_string(g.c) +
+                     ",\"lo\":" + std::to_string(g.lo) + ",\"g\":" + std::to_string(g.g) + ",\"ntiles\":" +
+                     std::to_string(g.ntiles) + ",\"phantom\":" + std::to_string(g.phantom) + ",\"blocks\":[";
+    for (size_t j = 0; j < g.blocks.size(); j++) {
+        js += (j ? "," : "") + std::string("{\"bits\":[");
+        for (size_t k = 0; k < g.blocks[j].size(); k++) js += (k ? "," : "") + std::to_string(g.blocks[j][k]);
+        js += "],\"fwd\":" + std::to_string(g.act_fwd[j]) + ",\"bwd\":" + std::to_string(g.act_bwd[j]) + ",\"dpp\":" +
+              std::to_string(g.dpp[j]) + "}";
+    }
+    return js + "]}";
+}
+
 extern "C" int sv_tune_describe(int n, sv_dtype dtype, char* buf, size_t len) {
     if (!buf || len == 0) return fail(SV_ERR_ARG, "sv_tune_describe: empty buffer");
     if (!dtype_ok(dtype)) return fail(SV_ERR_ARG, "sv_tune_describe: bad dtype");
@@ -1047,20 +1063,17 @@ extern "C" int sv_tune_describe(int n, sv_dtype dtype, char* buf, size_t len) {
         const char* key = fam == 0 ? "nv1" : (fam == 1 ? "grad_nv1" : "grad_nv2");
         js += std::string(fam == 0 ? "" : ",") + "\"" + key + "\":[";
         for (size_t i = 0; i < groups.size(); i++) {
-            const Geometry& g = groups[i];
-            js += (i ? "," : "") + std::string("{\"T\":") + std::to_string(g.T) + ",\"R\":" + std::to_string(g.R) +
-                  ",\"c\":" + std::to_string(g.c) + ",\"lo\":" + std::to_string(g.lo) + ",\"g\":" +
-                  std::to_string(g.g) + ",\"ntiles\":" + std::to_string(g.ntiles) + ",\"phantom\":" +
-                  std::to_string(g.phantom) + ",\"blocks\":[";
-            for (size_t j = 0; j < g.blocks.size(); j++) {
-                js += (j ? "," : "") + std::string("{\"bits\":[");
-                for (size_t k = 0; k < g.blocks[j].size(); k++)
-                    js += (k ? "," : "") + std::to_string(g.blocks[j][k]);
-                js += "],\"fwd\":" + std::to_string(g.act_fwd[j]) + ",\"bwd\":" + std::to_string(g.act_bwd[j]) +
-                      ",\"dpp\":" + std::to_string(g.dpp[j]) + "}";
-            }
-            js += "]}";
+            js += (i ? "," : "") + geometry_json(groups[i]);
         }
+        js += "]";
+    }
+    // the plan of forward programs where it has two groups (two_group_tiles) or small tiles
+    int T2 = 0;
+    const int tb = tile_bits(n, dtype);
+    if (tb > 0 || two_group_tiles(n, dtype, false, &T2)) {
+        const std::vector<Geometry> groups = tb > 0 ? tile_groups(n, tb) : two_groups(n, dtype, T2);
+        js += std::string(",\"") + (tb > 0 ? "small_tiles" : "two_groups") + "\":[";
+        for (size_t i = 0; i < groups.size(); i++) js += (i ? "," : "") + geometry_json(groups[i]);
         js += "]";
     }
     js += "}}";

@@ -173,8 +173,13 @@ int device_cu_count(int dev);  // compute units of a device (cached; 256 on MI35
 
 // ---------------------------------------------------------------- planning and execution
 std::vector<Geometry> plan_groups(int n, sv_dtype dt, int nv, bool grad = false, bool general = false);
-// tile_ok: the program may run on the small tiles (tile_bits), if its size takes them.
-Plan make_plan(int n, sv_dtype dt, bool grad = false, bool general = false, bool tile_ok = true);
+// base_tiles: the program needs the base tile shapes (general layers, adjoint forms).  tile_ok: it
+// may run on the small tiles (tile_bits), two_ok: on two groups (two_group_tiles), where its size
+// takes them.
+Plan make_plan(int n, sv_dtype dt, bool grad = false, bool base_tiles = false, bool tile_ok = true,
+               bool two_ok = true);
+bool two_group_tiles(int n, sv_dtype dt, bool base_tiles, int* T);
+std::vector<Geometry> two_groups(int n, sv_dtype dt, int T);
 int tile_bits(int n, sv_dtype dt);
 std::vector<Geometry> tile_groups(int n, int T);
 Program build_program(const std::vector<Event>& evs, int nres, bool fuse);
@@ -192,6 +197,8 @@ int gather_results(sv_state_s* s, const double* part, uint64_t ntiles, double* o
 // column, or the norm column (norm) signed by a bit of the tile index.
 void spin_segments(const Geometry& geo, int n, int col, int norm, std::vector<uint32_t>* segs);
 int prepare_passes(sv_state_s* s, sv_ising_s* H, const Program& prog, const Plan& plan);
+int prepare_tile_pass(sv_ising_s* H, hipStream_t stream, int dt, int T, int group, bool point);
+int prepare_energy_passes(sv_state_s* s, sv_ising_s* H);
 int fetch_results(sv_state_s* s, int nres);
 int ensure_work(sv_state_s* s, size_t part_doubles, size_t res_doubles);
 // Pinned staging buffer for nblk matrix blocks of general layers (waits until an earlier

@@ -73,6 +73,7 @@ std::map<std::string, int> g_knobs = {
                       // sweeps does not cancel in their difference)
     {"c128t14", 0},   // complex128 one-vector programs (not the adjoint): 1 = 14-bit tiles (512 threads,
                       // one workgroup per CU), 0 = 13-bit tiles (256 threads, two workgroups per CU)
+    {"twogroup", 1},  // 1: two tile groups (64-byte runs or larger tiles) where the plan would take three; 0: never
     {"tile", -1},     // small tiles of states that do not fill the chip: -1 by size (n <= 21), 0 never,
                       // 10..13 tiles of that many bits wherever two tile groups hold the state
     {"fail_next_launch", 0},  // 1: the next tile-pass launch reports a launch failure (error-path tests)
@@ -82,7 +83,7 @@ const std::map<std::string, std::pair<int, int>> g_knob_range = {
     {"fuse", {0, 1}},    {"cmin64", {0, 8}},   {"cmin128", {0, 8}},  {"ntmin", {0, 64}},   {"persist", {0, 8}},
     {"stagger", {0, 64}}, {"snake", {0, 2}},   {"dpp", {0, 1}},      {"ldsswz", {3, 5}},   {"batchwide", {0, 2}},
     {"batch128", {0, 1}}, {"c64t13", {0, 1}},  {"c64occ", {0, 1}},   {"c64g4", {0, 1}},    {"kc34", {0, 1}},
-    {"c64g14", {0, 2}},  {"ntinit", {0, 1}},   {"batchslab", {0, 4096}}, {"batchsphere", {0, 1}}, {"genunit", {0, 1}},   {"split", {0, 1}},    {"xcd", {-2, 5}},      {"c128t14", {0, 1}}, {"adjzeta", {-1, 1}}, {"tile", {-1, 13}},
+    {"c64g14", {0, 2}},  {"ntinit", {0, 1}},   {"batchslab", {0, 4096}}, {"batchsphere", {0, 1}}, {"genunit", {0, 1}},   {"split", {0, 1}},    {"xcd", {-2, 5}},      {"c128t14", {0, 1}}, {"adjzeta", {-1, 1}}, {"tile", {-1, 13}}, {"twogroup", {0, 1}},
     {"fail_next_launch", {0, 1}},
 };
 }  // namespace

@@ -245,6 +245,41 @@ std::vector<Geometry> plan_groups(int n, sv_dtype dt, int nv, bool grad, bool ge
     return out;
 }
 
+// Two tile groups instead of the three that plan_groups gives with 128-byte runs: one pass per
+// layer instead of two.  Up to one group bit more makes the runs of the strided group 64 bytes (a
+// rate of 3.5 instead of 4.5-5 TB/s: neighbouring tiles, which hold the other halves of the lines,
+// run at the same time on the same XCD), and larger tiles run one workgroup per CU (3.2-3.8 TB/s);
+// either way one such pass costs less than two (p = 8 energy evaluations):
+//   n = 24 complex128, 13-bit tiles, 64-byte runs:   1772 -> 1200 us
+//   n = 25 complex128, 14-bit tiles, 128-byte runs:  3346 -> 2736 us
+//   n = 26 complex128, 14-bit tiles, 64-byte runs:   6515 -> 5512 us
+//   n = 25 complex64, 14-bit tiles, 64-byte runs:    1895 -> 1276 us
+// Runs of 32 bytes lose (529 us a pass at n = 26 complex64 against 220), and so do 15-bit complex64
+// tiles (n = 26: 369-416 us a pass; observed runs 4775 against 3534 us).  base_tiles: programs whose
+// kernels exist for the 13-bit complex128 / 14-bit complex64 tiles only (Eq. AQA4 steps: n = 24
+// complex128, 10 steps, 2538 -> 1970 us).  Not for gate layers, whose passes take four layers at a
+// time and are bound by arithmetic (eight complex layers at n = 24: 1470 -> 1590 us), nor for the
+// complex128 adjoint, whose three-layout kernels spill (p = 8: 5.0 -> 6.1 ms).  Any plan
+// knob that is not at its default asks for plan_groups' plans.
+bool two_group_tiles(int n, sv_dtype dt, bool base_tiles, int* T) {
+    if (knob_for("twogroup", (int)dt, n) == 0 || knob_for("split", (int)dt, n) != 0) return false;
+    if (dt == SV_C128) {
+        if (knob_for("cmin128", (int)dt, n) != 3 || knob_for("c128t14", (int)dt, n) != 0) return false;
+        *T = n == 24 ? 13 : 14;
+        return n == 24 || (!base_tiles && (n == 25 || n == 26));
+    }
+    if (knob_for("cmin64", (int)dt, n) != 4 || knob_for("c64occ", (int)dt, n) != 1 || knob_for("c64t13", (int)dt, n) != 0)
+        return false;
+    *T = 14;
+    return n == 25;
+}
+
+std::vector<Geometry> two_groups(int n, sv_dtype dt, int T) {
+    const int G = swz_bits(dt), g = n - T;
+    const uint32_t dpp = knob_for("dpp", (int)dt, n) == 0 ? 0u : 0x8u;
+    return {make_geometry(n, T, 5, T, T, 0, G, dpp, true), make_geometry(n, T, 5, T - g, T, g, G, dpp, true)};
+}
+
 // Groups of a small-tile plan: two at most (n <= 2 T - 3), no lane butterflies, whole-tile
 // exchanges (all four register slots free).
 std::vector<Geometry> tile_groups(int n, int T) {
@@ -815,7 +850,7 @@ double ground_tol(const sv_ising_s* H) { return H->qden > 0 ? 0.0 : 1e-9 * std::
 
 
 // grad: the adjoint family, whose one- and two-vector tiles share T.
-Plan make_plan(int n, sv_dtype dt, bool grad, bool general, bool tile_ok) {
+Plan make_plan(int n, sv_dtype dt, bool grad, bool base_tiles, bool tile_ok, bool two_ok) {
     Plan pl;
     // small tiles (complex128 two-vector programs, chosen by knob adjzeta only, have no kernels there)
     const int tb = tile_ok && !(grad && dt == SV_C128) ? tile_bits(n, dt) : 0;
@@ -824,11 +859,16 @@ Plan make_plan(int n, sv_dtype dt, bool grad, bool general, bool tile_ok) {
         pl.by_nv[1] = pl.by_nv[2] = tile_groups(n, tb);
         return pl;
     }
+    int T2 = 0;
+    if (!grad && two_ok && two_group_tiles(n, dt, base_tiles, &T2)) {
+        pl.by_nv[1] = pl.by_nv[2] = two_groups(n, dt, T2);
+        return pl;
+    }
     // complex64 one-vector programs may use the 13-bit tiles of the adjoint family
     // (not programs with general single-qubit layers, whose kernels exist for 14-bit tiles)
-    if (dt == SV_C64 && !general && knob_for("c64t13", (int)dt, n) != 0) grad = true;
-    pl.by_nv[1] = plan_groups(n, dt, 1, grad, general);
-    pl.by_nv[2] = plan_groups(n, dt, 2, grad, general);
+    if (dt == SV_C64 && !base_tiles && knob_for("c64t13", (int)dt, n) != 0) grad = true;
+    pl.by_nv[1] = plan_groups(n, dt, 1, grad, base_tiles);
+    pl.by_nv[2] = plan_groups(n, dt, 2, grad, base_tiles);
     return pl;
 }
 
@@ -1057,8 +1097,11 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
         a.nslots = (int)p.slot_dst.size();
         a.nops = 0;
         a.need_e = 0;
-        a.nt = (geo.phantom == 0 && geo.c >= ntmin) ? 3 : 0;
-        if (geo.phantom == 0 && (p.load & 4) && knob_for("ntinit", (int)s->dt, s->n) != 0) a.nt = 3;
+        // (states of 128 and 256 MiB stay in the last-level cache between passes: plain accesses are
+        // 2-9 % faster there, n = 24 complex128 1257 -> 1200 us, and 6 % slower at 64 MiB)
+        const bool cached = s->bytes > (size_t(64) << 20) && s->bytes <= (size_t(256) << 20);
+        a.nt = (geo.phantom == 0 && geo.c >= ntmin && !cached) ? 3 : 0;
+        if (geo.phantom == 0 && !cached && (p.load & 4) && knob_for("ntinit", (int)s->dt, s->n) != 0) a.nt = 3;
         a.swz = lds_swz_bits(s->dt, s->n);
         a.grid = persist * ncu;
         a.stagger = stagger;
@@ -1181,9 +1224,8 @@ int prepare_passes(sv_state_s* s, sv_ising_s* H, const Program& prog, const Plan
         bool point = false;
         for (const Op& op : p.ops) point = point || op.kind == OP_POINT;
         if (plan.tile) {
-            std::lock_guard<std::mutex> g(H->mu);
-            H->tile_seen.insert(std::make_tuple((int)s->dt, plan.by_nv[1][0].T, p.group, point));
-            if (point) H->tile_seen.insert(std::make_tuple((int)s->dt, plan.by_nv[1][0].T, p.group, false));
+            int rc = prepare_tile_pass(H, s->stream, (int)s->dt, plan.by_nv[1][0].T, p.group, point);
+            if (rc) return rc;
             continue;
         }
         const Geometry& geo = plan.by_nv[p.nv][p.group];
@@ -1191,6 +1233,22 @@ int prepare_passes(sv_state_s* s, sv_ising_s* H, const Program& prog, const Plan
         int rc = get_geobuf(geo, H, s->dt, &gb);
         const double* tf = nullptr;
         if (!rc && point) rc = get_tf(H, geo, gb, s->stream, &tf);
+        if (rc) return rc;
+    }
+    return SV_OK;
+}
+
+// The same for a call whose own plan has three groups where energy evaluations have two
+// (two_group_tiles): energy evaluations that may not build tables follow it as they did when the
+// plans were one.
+int prepare_energy_passes(sv_state_s* s, sv_ising_s* H) {
+    int T2 = 0;
+    if (!two_group_tiles(s->n, s->dt, false, &T2)) return SV_OK;
+    for (const Geometry& geo : two_groups(s->n, s->dt, T2)) {
+        GeoBuf* gb = nullptr;
+        const double* tf = nullptr;
+        int rc = get_geobuf(geo, H, s->dt, &gb);
+        if (!rc) rc = get_tf(H, geo, gb, s->stream, &tf);
         if (rc) return rc;
     }
     return SV_OK;
@@ -1292,10 +1350,18 @@ int run_ground(sv_ising_s* H, hipStream_t stream) {
         std::lock_guard<std::mutex> g(H->mu);
         if (H->has_ground) return SV_OK;
     }
+    const sv_dtype dt = SV_C64;  // enumeration tiles use the complex64 tile shape
+    if (const int tb = tile_bits(H->n, dt); tb > 0 && H->n <= 14) {
+        // complex64 energy evaluations of up to 14 qubits need no table beyond this one: those that
+        // may not build any (tile_seen) follow sv_ground alone
+        for (int grp = 0; grp < 2; grp++) {
+            int rc = prepare_tile_pass(H, stream, (int)dt, tb, grp, true);
+            if (rc) return rc;
+        }
+    }
     int done = 0;
     int rc = run_ground_sets(H, stream, &done);
     if (rc || done) return rc;
-    const sv_dtype dt = SV_C64;  // enumeration tiles use the complex64 tile shape
     const Shape sh = shape_for((int)dt, 1, false);
     std::vector<Geometry> groups = plan_groups(H->n, dt, 1);
     const Geometry& geo = groups[0];

@@ -46,6 +46,17 @@ static int get_etab(sv_ising_s* H, hipStream_t stream, const double** out, bool 
     return SV_OK;
 }
 
+// Records a small-tile pass as a run of it would (tile_seen) and builds the energy table it reads.
+int prepare_tile_pass(sv_ising_s* H, hipStream_t stream, int dt, int T, int group, bool point) {
+    const double* E = nullptr;
+    int rc = get_etab(H, stream, &E, false);
+    if (rc) return rc;
+    std::lock_guard<std::mutex> g(H->mu);
+    H->tile_seen.insert(std::make_tuple(dt, T, group, point));
+    if (point) H->tile_seen.insert(std::make_tuple(dt, T, group, false));
+    return SV_OK;
+}
+
 // 4 J over the pairs of register bits set in r, for the layout that starts at tile bit b.
 static void register_couplings(const Geometry& geo, const sv_ising_s* H, int b, double* Q) {
     int slot[64];

@@ -831,14 +831,10 @@ static int grad_zeta(sv_state_s* psi, sv_state_s* lam, sv_ising_s* H, int p, con
     if (rc) return rc;
     rc = run_program(psi, nullptr, H, minus, plan, false);
     if (rc) return rc;
-    hipError_t e = hipStreamSynchronize(psi->stream);
-    if (e != hipSuccess) {
-        psi->failed = true;
-        return fail(SV_ERR_HIP, "sv_grad: %s", hipGetErrorString(e));
-    }
-    rc = fetch_results(lam, 2 * p + 3);
-    if (rc) return rc;
+    // psi's results come last on the stream both programs ran on
     rc = fetch_results(psi, 2 * p);
+    if (rc) return rc;
+    rc = fetch_results(lam, 2 * p + 3);
     if (rc) return rc;
     rc = prepare_energy_passes(psi, H);
     if (rc) return rc;

@@ -44,6 +44,9 @@ bool prof_begin(hipStream_t st, hipEvent_t* a);
 void prof_end(hipStream_t st, hipEvent_t a, const std::string& kind, double bytes);
 
 // ---------------------------------------------------------------- objects
+// Marks a result that a kernel has yet to write: a NaN that arithmetic does not produce.
+constexpr uint64_t kAwaited = 0x7ff8a1d25ec0de01ull;
+
 struct Work {
     double2* d_tab = nullptr;
     size_t tab_cap = 0;  // double2
@@ -53,6 +56,7 @@ struct Work {
     double* h_res = nullptr;
     size_t res_cap = 0;  // doubles
     bool res_on_host = false;  // the last program wrote its results to h_res itself
+    int awaited = 0;  // its last kernel writes this many results over kAwaited (0: wait for the stream)
     double* d_spin = nullptr;  // per-tile spin partials [kTF][ntiles]
     size_t spin_cap = 0;       // doubles
     double* d_gmat = nullptr;  // general single-qubit layers, kGenBlock doubles per MIX op
@@ -198,6 +202,7 @@ int gather_results(sv_state_s* s, const double* part, uint64_t ntiles, double* o
 void spin_segments(const Geometry& geo, int n, int col, int norm, std::vector<uint32_t>* segs);
 int prepare_passes(sv_state_s* s, sv_ising_s* H, const Program& prog, const Plan& plan);
 int prepare_tile_pass(sv_ising_s* H, hipStream_t stream, int dt, int T, int group, bool point);
+int drop_results(sv_state_s* s);
 int prepare_energy_passes(sv_state_s* s, sv_ising_s* H);
 int fetch_results(sv_state_s* s, int nres);
 int ensure_work(sv_state_s* s, size_t part_doubles, size_t res_doubles);

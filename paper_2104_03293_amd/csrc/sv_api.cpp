@@ -1022,7 +1022,7 @@ static std::string geometry_json(const Geometry& g) {
         js += (j ? "," : "") + std::string("{\"bits\":[");
         for (size_t k = 0; k < g.blocks[j].size(); k++) js += (k ? "," : "") + std::to_string(g.blocks[j][k]);
         js += "],\"fwd\":" + std::to_string(g.act_fwd[j]) + ",\"bwd\":" + std::to_string(g.act_bwd[j]) + ",\"dpp\":" +
-              std::to_string(g.dpp[j]) + "}";
+              std::to_string(g.dpp[j]) + (g.pairs.empty() ? "" : ",\"pair\":" + std::to_string(g.pairs[j])) + "}";
     }
     return js + "]}";
 }

@@ -123,6 +123,7 @@ struct Geometry {
     std::vector<std::vector<int>> blocks;  // register bit blocks per layout
     std::vector<uint32_t> act_fwd, act_bwd;
     std::vector<uint32_t> dpp;  // per layout: lane positions butterflied across lanes (bit 3 or 4)
+    std::vector<int> pairs;     // small tiles, per layout: first of the two tile bits in lane bits 4 and 5
     bool pivot = true;          // layouts share tile bit T-1 in register slot R-1 (half-tile exchanges)
 };
 

@@ -259,8 +259,8 @@ int launch_ground_sets(const GroundSetArgs& a, int nblocks, void* stream);
 
 // ---------------------------------------------------------------- small tiles
 // Tile programs of states that the large tiles cannot spread over the chip
-// (sv_tile.hip).  Layout j of a tile holds tile bits [lb, lb + 4) in registers,
-// lb = (lbpack >> 8j) & 255.  Reduction columns: part[column][tile].
+// (sv_tile.hip).  Layout j of a tile holds tile bits [b, b + 4) in registers and
+// q, q + 1 in lane bits 4 and 5, b | q << 4 = (lbpack >> 8j) & 255.  Reduction columns: part[column][tile].
 constexpr int kTileR = 4;
 constexpr int kMaxTileOps = 104;
 constexpr double kTileMaxAngle = 65536.0;  // phase angles gamma * E beyond it use the large tiles
@@ -283,7 +283,8 @@ struct TileArgs {
     uint32_t phantom;
     int32_t nlayouts;
     uint32_t lbpack;
-    uint32_t act_fwd, act_bwd;  // active register slots of layout j: bits 8j .. 8j + 3
+    uint32_t act;           // layout j: bits 8j .. 8j + 3 active register slots, 8j + 4 and 8j + 5 active
+                            //   lane bits 4 and 5 (only in the first and the last layout)
     int32_t load, store;    // as PassArgs
     int32_t need_e;         // bit 0: a point op runs in layout 0, bit 1: in the last layout
     int32_t nops;

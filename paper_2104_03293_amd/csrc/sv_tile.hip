@@ -12,12 +12,14 @@
 // phase factors are computed in place instead of by a launch of their own, and
 // the code is a loop over ops and layouts (one copy of each op's code).
 // Measured against the large tiles: n = 12 complex64, p = 4 (one launch) 93 ->
-// 20 us per evaluation, n = 20 complex64, p = 8 255 -> 132 us, n = 21 real
-// couplings, p = 3 164 -> 92 us, n = 17 gradient, p = 4 436 -> 159 us.  Cycle
-// stamps of one workgroup (n = 18, 2^11 tiles): start and loads 2500, a mixer
-// round 900 of arithmetic and 1300 of exchange, a phase 2700, a reduction 2300,
-// store 900.
+// 20 us per evaluation, n = 20 complex64, p = 8 255 -> 117 us, n = 21 real
+// couplings, p = 3 164 -> 86 us, n = 17 gradient, p = 4 436 -> 145 us.  Cycle
+// stamps of one workgroup (n = 12, double precision in registers): a mixer round
+// 900, a swap of two lane bits 500, an exchange 1500, a phase 2700, a reduction
+// 2300; start and loads 2100.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "sv_device.h"
 #include "sv_internal.h"
@@ -90,10 +92,40 @@ __device__ __forceinline__ void block_sums(double (&v)[N], double (*s_red)[kTF],
 __device__ __forceinline__ uint32_t tile_slot(uint32_t u) { return u ^ (((u >> 4) ^ (u >> 8) ^ (u >> 12)) & 15u); }
 __device__ __forceinline__ uint32_t tile_slot_bit(int p) { return (1u << p) | (p >= 4 ? 1u << (p & 3) : 0u); }
 
+// Exchanges lane bit B (4 or 5) of a wave with the choice of register: the lanes of a with the bit
+// set take those of b with it clear, and the other way round.
+template <int B>
+__device__ __forceinline__ void lane_swap(uint32_t& a, uint32_t& b) {
+    const auto x = B == 4 ? __builtin_amdgcn_permlane16_swap(a, b, false, false)
+                          : __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = x[0];
+    b = x[1];
+}
+template <int B>
+__device__ __forceinline__ void lane_swap(float& a, float& b) {
+    uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+    lane_swap<B>(x, y);
+    a = __uint_as_float(x);
+    b = __uint_as_float(y);
+}
+template <int B>
+__device__ __forceinline__ void lane_swap(double& a, double& b) {
+    const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+    uint32_t xl = (uint32_t)x, xh = (uint32_t)(x >> 32), yl = (uint32_t)y, yh = (uint32_t)(y >> 32);
+    lane_swap<B>(xl, yl);
+    lane_swap<B>(xh, yh);
+    a = __longlong_as_double((long long)((uint64_t)xh << 32 | xl));
+    b = __longlong_as_double((long long)((uint64_t)yh << 32 | yl));
+}
+
 // One tile program.  Real: stored amplitudes; Acc: amplitudes in registers and
 // LDS; 2^T amplitudes per workgroup, 2^R per thread and vector, NV vectors.
-// Layout j holds tile bits [lb[j], lb[j] + R) in registers and the others in
-// the thread index, in order.  FEAT: 0 uniform mixers, phases and the energy
+// Layout j holds tile bits [b, b + 4) in registers, q and q + 1 in lane bits 4
+// and 5, and the others in the rest of the thread index, in order.  A layout
+// with butterflies on q and q + 1 swaps them with register slots 2 and 3 by
+// permlane swaps (an eighth of an exchange through LDS), so that the next
+// exchange leaves from, or arrives in, the swapped form; points, loads and
+// stores see the plain one.  FEAT: 0 uniform mixers, phases and the energy
 // reduction; 1 also the forms of the adjoint sweeps; 2 also general layers and
 // spin sums (each left out where it is not needed: registers and code size).
 template <typename Real, typename Acc, int T, int R, int NV, int FEAT>
@@ -110,7 +142,7 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
     // every scalar of the header at once (the compiler would fetch them block by block, a memory
     // round trip each)
     asm volatile("" ::"s"(a.psi), "s"(a.lam), "s"(a.src), "s"(a.E), "s"(a.part), "s"(a.c), "s"(a.lo), "s"(a.g));
-    asm volatile("" ::"s"(a.phantom), "s"(a.nlayouts), "s"(a.lbpack), "s"(a.act_fwd), "s"(a.act_bwd), "s"(a.load),
+    asm volatile("" ::"s"(a.phantom), "s"(a.nlayouts), "s"(a.lbpack), "s"(a.act), "s"(a.load),
                  "s"(a.store), "s"(a.need_e), "s"(a.nops), "s"(a.dual), "s"(a.amp0));
     const uint32_t t = threadIdx.x;
     // the op list is read where it lies (a dynamic index into a by-value
@@ -130,11 +162,21 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
     const uint32_t ph = a.phantom;
     double* const part = a.part + (second ? (uint64_t)a.dual_cols * a.ntiles : 0ull);
 
-    auto lbase = [&](int j) { return (a.lbpack >> (8 * j)) & 255; };
-    auto tpart = [&](int b) { return (t & ((1u << b) - 1u)) | ((t >> b) << (b + R)); };
+    auto lbase = [&](int j) { return (int)((a.lbpack >> (8 * j)) & 15u); };
+    auto lpair = [&](int j) { return (int)((a.lbpack >> (8 * j + 4)) & 15u); };
+    // tile bits of the thread index but lane bits 4 and 5, and of all of it
+    auto trest = [&](int b, int q) {
+        const uint32_t y = (t & 15u) | ((t >> 6) << 4);
+        const int g1 = min(b, q), g2 = max(b, q), w1 = b < q ? R : 2, w2 = b < q ? 2 : R;
+        const uint32_t z = (y & ((1u << g1) - 1u)) | ((y >> g1) << (g1 + w1));
+        return (z & ((1u << g2) - 1u)) | ((z >> g2) << (g2 + w2));
+    };
+    const uint32_t tl = (t >> 4) & 3u;
+    auto tpart = [&](int j) { return trest(lbase(j), lpair(j)) | tl << lpair(j); };
+    auto swaps = [&](int j) { return ((a.act >> (8 * j)) & 0x30u) != 0u; };
     int cur = 0;
     int ab = lbase(0);
-    uint32_t thr = tpart(ab);
+    uint32_t thr = tpart(0);
 
     // Byte offsets of 32 bits (the states here hold less than 2^28 bytes); register r = i ^ (i >> 1)
     // is reached by one XOR from register (i - 1) ^ ((i - 1) >> 1).
@@ -191,7 +233,7 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
         ql[s] = 0.0;
         if ((a.need_e >> s) & 1) {
             const int b = lbase(s ? K - 1 : 0);
-            const uint32_t u = tpart(b);
+            const uint32_t u = tpart(s ? K - 1 : 0);
             const char* __restrict__ E = reinterpret_cast<const char*>(a.E);
             const uint32_t o = (base32 | goff(u)) * 8u;
             ev[s][0] = *reinterpret_cast<const double*>(E + o);
@@ -205,6 +247,72 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
     double pend[NV];  // uniform scale every register of vector v still has to be multiplied by
 #pragma unroll
     for (int v = 0; v < NV; v++) pend[v] = 1.0;
+
+    // register slots 2 and 3 <-> lane bits 4 and 5
+    auto swap45 = [&]() {
+#pragma unroll
+        for (int v = 0; v < NV; v++)
+#pragma unroll
+            for (int r = 0; r < NR; r++) {
+                if (!(r & 4)) {
+                    lane_swap<4>(vr[v][r], vr[v][r | 4]);
+                    lane_swap<4>(vi[v][r], vi[v][r | 4]);
+                }
+            }
+#pragma unroll
+        for (int v = 0; v < NV; v++)
+#pragma unroll
+            for (int r = 0; r < NR; r++) {
+                if (!(r & 8)) {
+                    lane_swap<5>(vr[v][r], vr[v][r | 8]);
+                    lane_swap<5>(vi[v][r], vi[v][r | 8]);
+                }
+            }
+    };
+    // LDS exchange into layout j, between the swapped forms of layouts that swap.  A thread writes
+    // only the slots it read last, so one barrier (between writes and reads) is enough.
+    auto exchange = [&](int j) {
+        const bool ws = swaps(cur), wd = swaps(j);
+        const int nb = lbase(j), sq = lpair(cur), dq = lpair(j);
+        constexpr uint32_t SZ = (uint32_t)sizeof(A2);
+        uint32_t bs[R], bd[R];
+#pragma unroll
+        for (int k = 0; k < R; k++) {
+            bs[k] = tile_slot_bit(k >= 2 && ws ? sq + k - 2 : ab + k) * SZ;
+            bd[k] = tile_slot_bit(k >= 2 && wd ? dq + k - 2 : nb + k) * SZ;
+        }
+        const uint32_t nrest = trest(nb, dq);
+        const uint32_t s0 = tile_slot((thr & ~(3u << sq)) | tl << (ws ? ab + 2 : sq)) * SZ;
+        const uint32_t d0 = tile_slot(nrest | tl << (wd ? nb + 2 : dq)) * SZ;
+        char* xb = reinterpret_cast<char*>(xbuf);
+#pragma unroll
+        for (int v = 0; v < NV; v++) {
+            if (v > 0) __syncthreads();  // the first vector's reads
+            uint32_t ad = s0;
+#pragma unroll
+            for (int i = 0; i < NR; i++) {
+                if (i > 0) ad ^= bs[__builtin_ctz(i)];
+                const int r = i ^ (i >> 1);
+                A2 x;
+                x.x = vr[v][r];
+                x.y = vi[v][r];
+                *reinterpret_cast<A2*>(xb + ad) = x;
+            }
+            __syncthreads();
+            ad = d0;
+#pragma unroll
+            for (int i = 0; i < NR; i++) {
+                if (i > 0) ad ^= bd[__builtin_ctz(i)];
+                const int r = i ^ (i >> 1);
+                const A2 x = *reinterpret_cast<const A2*>(xb + ad);
+                vr[v][r] = x.x;
+                vi[v][r] = x.y;
+            }
+        }
+        cur = j;
+        ab = nb;
+        thr = nrest | tl << dq;
+    };
 
     // the next op is fetched while one runs
     uint32_t nw0 = op0.w0;
@@ -232,59 +340,16 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
             const bool fwd = cur == 0;
             double gsum = 0.0;
             const Acc tq = (Acc)opa;
-#pragma unroll 1
-            for (int step = 0; step < K; step++) {
-                const int j = fwd ? step : K - 1 - step;
-                if (step > 0) {
-                    // LDS exchange into layout j.  A thread writes only the slots it read
-                    // last, so one barrier (between writes and reads) is enough.
-                    const int nb = lbase(j);
-                    const uint32_t nthr = tpart(nb);
-                    constexpr uint32_t SZ = (uint32_t)sizeof(A2);
-                    uint32_t bs[R], bd[R];
-#pragma unroll
-                    for (int k = 0; k < R; k++) {
-                        bs[k] = tile_slot_bit(ab + k) * SZ;
-                        bd[k] = tile_slot_bit(nb + k) * SZ;
-                    }
-                    const uint32_t s0 = tile_slot(thr) * SZ, d0 = tile_slot(nthr) * SZ;
-                    char* xb = reinterpret_cast<char*>(xbuf);
-#pragma unroll
-                    for (int v = 0; v < NV; v++) {
-                        if (v > 0) __syncthreads();  // the first vector's reads
-                        uint32_t ad = s0;
-#pragma unroll
-                        for (int i = 0; i < NR; i++) {
-                            if (i > 0) ad ^= bs[__builtin_ctz(i)];
-                            const int r = i ^ (i >> 1);
-                            A2 x;
-                            x.x = vr[v][r];
-                            x.y = vi[v][r];
-                            *reinterpret_cast<A2*>(xb + ad) = x;
-                        }
-                        __syncthreads();
-                        ad = d0;
-#pragma unroll
-                        for (int i = 0; i < NR; i++) {
-                            if (i > 0) ad ^= bd[__builtin_ctz(i)];
-                            const int r = i ^ (i >> 1);
-                            const A2 x = *reinterpret_cast<const A2*>(xb + ad);
-                            vr[v][r] = x.x;
-                            vi[v][r] = x.y;
-                        }
-                    }
-                    cur = j;
-                    ab = nb;
-                    thr = nthr;
-                }
-                const int act = (int)(((fwd ? a.act_fwd : a.act_bwd) >> (8 * j)) & 255u);
+            // butterflies of register slots K0 .. 3; slot 0 or 2 holds tile bit p0 or p2
+            auto round = [&](auto k0, uint32_t act, int p0, int p2) {
+                constexpr int K0 = decltype(k0)::value;
                 if (FEAT == 2 && (fl & MIX_GEN)) {
                     // general single-qubit layer: (u, v) <- (m00 u + m01 v, m10 u + m11 v)
                     const SV_CONST double* M = (const SV_CONST double*)(a.gmat + (uint64_t)aux * kGenBlock);
 #pragma unroll
-                    for (int k = 0; k < R; k++) {
+                    for (int k = K0; k < R; k++) {
                         if (!((act >> k) & 1)) continue;
-                        const SV_CONST double* m = M + 8 * (ab + k);
+                        const SV_CONST double* m = M + 8 * (k < 2 ? p0 + k : p2 + k - 2);
                         const Acc a0 = (Acc)m[0], a1 = (Acc)m[1], b0 = (Acc)m[2], b1 = (Acc)m[3];
                         const Acc c0 = (Acc)m[4], c1 = (Acc)m[5], d0 = (Acc)m[6], d1 = (Acc)m[7];
 #pragma unroll
@@ -298,10 +363,10 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
                             vi[0][r2] = fma(c0, ui, fma(c1, ur, fma(d0, wi, d1 * wr)));
                         }
                     }
-                    continue;
+                    return;
                 }
 #pragma unroll
-                for (int k = 0; k < R; k++) {
+                for (int k = K0; k < R; k++) {
                     // a slot that is not active here runs identity butterflies (t = 0): a branch
                     // would copy the amplitude registers at its join
                     const bool on = (act >> k) & 1;
@@ -337,7 +402,7 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
                     // values after the round (a butterfly leaves the form of every qubit unchanged)
                     double g2[2] = {0.0, 0.0};
 #pragma unroll
-                    for (int k = 0; k < R; k++) {
+                    for (int k = K0; k < R; k++) {
                         if (!((act >> k) & 1)) continue;
 #pragma unroll
                         for (int r = 0; r < NR; r++) {
@@ -348,6 +413,27 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
                         }
                     }
                     gsum += 2.0 * (g2[0] + g2[1]) * pend[0] * pend[0];
+                }
+            };
+            using S0 = std::integral_constant<int, 0>;
+            using S2 = std::integral_constant<int, 2>;
+#pragma unroll 1
+            for (int step = 0; step < K; step++) {
+                const int j = fwd ? step : K - 1 - step;
+                const uint32_t act = (a.act >> (8 * j)) & 255u;
+                const bool sw = (act & 0x30u) != 0u;
+                if (step > 0) {
+                    exchange(j);
+                    if (sw) {  // the layout a mixer ends in
+                        round(S2{}, act >> 2, 0, lpair(j));
+                        swap45();
+                    }
+                }
+                round(S0{}, act & 15u, ab, ab + 2);
+                if (step == 0 && sw) {  // the layout it begins in
+                    swap45();
+                    round(S2{}, act >> 2, 0, lpair(j));
+                    if (K == 1) swap45();
                 }
             }
             if (FEAT == 1 && (fl & MIX_GBETA)) {
@@ -393,13 +479,12 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
             const double nrm = rv[0] * s2;
             if (FEAT == 2 && (fl & PT_SPINZ)) {
                 // entry l < T: sum of |psi|^2 s_l over the tile, entry T: sum of |psi|^2
-                // (tile bit l is register bit l - ab or thread bit l or l - R)
+                // (tile bit l is register bit l - ab or a bit of thr)
                 double sv[T + 1];
 #pragma unroll
                 for (int l = 0; l < T; l++) {
                     const int k = l - ab;
-                    const int j = l < ab ? l : l - R;
-                    double x = ((t >> (j & 31)) & 1u) ? nrm : -nrm;
+                    double x = ((thr >> l) & 1u) ? nrm : -nrm;
 #pragma unroll
                     for (int q = 0; q < R; q++)
                         if (k == q) x = Sk[q] * s2;
@@ -487,7 +572,12 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
         }
     }
 
-    // ---- store in the current layout
+    // ---- store, in layout 0 (the last layout holds the lowest tile bits in registers)
+    if (cur != 0 && a.store != 0) {
+        if (swaps(cur)) swap45();
+        exchange(0);
+        if (swaps(0)) swap45();
+    }
     {
         uint32_t gb[R];
 #pragma unroll

@@ -258,9 +258,8 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
         a.phantom = geo.phantom;
         a.nlayouts = (int)geo.blocks.size();
         for (int j = 0; j < a.nlayouts; j++) {
-            a.lbpack |= (uint32_t)geo.blocks[j][0] << (8 * j);
-            a.act_fwd |= geo.act_fwd[j] << (8 * j);
-            a.act_bwd |= geo.act_bwd[j] << (8 * j);
+            a.lbpack |= (uint32_t)(geo.blocks[j][0] | geo.pairs[j] << 4) << (8 * j);
+            a.act |= (geo.act_fwd[j] | geo.dpp[j]) << (8 * j);
         }
         a.load = L.load;
         a.store = dual ? 0 : L.store;

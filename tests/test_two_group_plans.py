@@ -33,6 +33,18 @@ def test_plans_cover_every_qubit_and_amplitude(sv, dtype, n):
                 assert len(set(blk["bits"])) == R and max(blk["bits"]) < T
                 seen += [blk["bits"][k] for k in range(R) if blk[direction] >> k & 1]
                 tb = [l for l in range(T) if l not in blk["bits"]]
+                if "pair" in blk:  # small tiles: lane bits 4 and 5 hold pair and pair + 1
+                    p = blk["pair"]
+                    tb = [l for l in tb if l not in (p, p + 1)]
+                    assert len(tb) == T - R - 2 and p + 1 < T
+                    tb[4:4] = [p, p + 1]
+                    # 16 lanes of an exchange reach 16 different LDS slots (either form of the layout)
+                    slot = lambda l: 1 << l | (1 << (l & 3) if l >= 4 else 0)
+                    low = {0}
+                    for l in tb[:4]:
+                        low |= {x ^ (slot(l) & 15) for x in low}
+                    assert len(low) == 16
+                    assert blk["dpp"] & ~0x30 == 0 and (not blk["dpp"] or blk in (g["blocks"][0], g["blocks"][-1]))
                 seen += [tb[q] for q in range(6) if blk["dpp"] >> q & 1]
             assert sorted(seen) == active
         if n > T:  # tile index and tile bits together address every amplitude once

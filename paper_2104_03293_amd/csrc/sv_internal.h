@@ -263,6 +263,8 @@ int launch_ground_sets(const GroundSetArgs& a, int nblocks, void* stream);
 // q, q + 1 in lane bits 4 and 5, b | q << 4 = (lbpack >> 8j) & 255.  Reduction columns: part[column][tile].
 constexpr int kTileR = 4;
 constexpr int kMaxTileOps = 104;
+// Phase table entries: with 512 of 16 bytes two workgroups of 2^12 complex128 amplitudes still share a CU.
+constexpr int kTileLut = 512;
 constexpr double kTileMaxAngle = 65536.0;  // phase angles gamma * E beyond it use the large tiles
 struct TileOp {
     uint32_t w0;   // OpKind | MixFlags / PointFlags << 8
@@ -293,6 +295,8 @@ struct TileArgs {
     int32_t dual_cols;      //   writing its columns dual_cols further on
     int32_t resident;       // the program runs in one launch of one workgroup
     int32_t feat;           // kernel variant: 0 plain, 1 adjoint forms, 2 general layers and spin sums
+    int32_t lut_n;          // energies lie on (2 i - lut_n + 1) lut_step, 0 <= i < lut_n; 0: no phase table
+    double lut_step;
     double emin, etol, amp0;
     double Q[2][1 << kTileR];  // layout 0 and the last: sum of 4 J over the register-bit pairs set in r
     TileOp ops[kMaxTileOps];

@@ -12,11 +12,11 @@
 // phase factors are computed in place instead of by a launch of their own, and
 // the code is a loop over ops and layouts (one copy of each op's code).
 // Measured against the large tiles: n = 12 complex64, p = 4 (one launch) 93 ->
-// 20 us per evaluation, n = 20 complex64, p = 8 255 -> 117 us, n = 21 real
+// 19 us per evaluation, n = 20 complex64, p = 8 255 -> 114 us, n = 21 real
 // couplings, p = 3 164 -> 86 us, n = 17 gradient, p = 4 436 -> 145 us.  Cycle
 // stamps of one workgroup (n = 12, double precision in registers): a mixer round
-// 900, a swap of two lane bits 500, an exchange 1500, a phase 2700, a reduction
-// 2300; start and loads 2100.
+// 900, a swap of two lane bits 500, an exchange 1500, a phase from the table
+// 2300 (in place 2700), a reduction 2300; start and loads 2100.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -138,12 +138,13 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
     static_assert(NT >= 64 && R == 4, "whole waves, 16 amplitudes per thread");
     __shared__ A2 xbuf[1 << T];
     __shared__ double s_red[NW][kTF];
+    __shared__ A2 s_lut[kTileLut];  // phase factors of a grid-valued instance
 
     // every scalar of the header at once (the compiler would fetch them block by block, a memory
     // round trip each)
     asm volatile("" ::"s"(a.psi), "s"(a.lam), "s"(a.src), "s"(a.E), "s"(a.part), "s"(a.c), "s"(a.lo), "s"(a.g));
     asm volatile("" ::"s"(a.phantom), "s"(a.nlayouts), "s"(a.lbpack), "s"(a.act), "s"(a.load),
-                 "s"(a.store), "s"(a.need_e), "s"(a.nops), "s"(a.dual), "s"(a.amp0));
+                 "s"(a.store), "s"(a.need_e), "s"(a.nops), "s"(a.dual), "s"(a.lut_n), "s"(a.lut_step), "s"(a.amp0));
     const uint32_t t = threadIdx.x;
     // the op list is read where it lies (a dynamic index into a by-value
     // argument would copy it to scratch memory)
@@ -539,7 +540,48 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
                 block_sums<1, NW>(gv, s_red, put_at(part2));
             }
         }
-        if (fl & (PT_PHASE_PSI | PT_PHASE_LAM)) {
+        if ((fl & (PT_PHASE_PSI | PT_PHASE_LAM)) && a.lut_n > 0) {
+            // Energies on the grid (2 i - lut_n + 1) / q, 0 <= i < lut_n: the factors of all of them,
+            // with the pending scale, in LDS; then one look-up per amplitude (220 instructions per
+            // thread and phase instead of 540).
+            double sc = 1.0;
+            if constexpr (NV == 1) {
+                sc = pend[0];
+                pend[0] = 1.0;
+            }
+            __syncthreads();  // the look-ups of the phase before
+            for (int i = (int)t; i < a.lut_n; i += NT) {
+                const double2 f = cis_neg(opa * ((double)(2 * i - a.lut_n + 1) * a.lut_step));
+                A2 x;
+                x.x = (Acc)(f.x * sc);
+                x.y = (Acc)(f.y * sc);
+                s_lut[i] = x;
+            }
+            const double hq = 0.5 / a.lut_step;
+            constexpr int LS = (int)sizeof(A2);
+            int run = (int)fma(e0, hq, 0.5 * (double)(a.lut_n - 1)) * LS;
+            const int qi = (int)((es ? ql[1] : ql[0]) * hq) * LS;
+            int di[R];
+#pragma unroll
+            for (int k = 0; k < R; k++) di[k] = (int)(d[k] * hq) * LS;
+            __syncthreads();
+            const char* lut = reinterpret_cast<const char*>(s_lut);
+#pragma unroll
+            for (int i = 0; i < NR; i++) {
+                const int r = i ^ (i >> 1);
+                if (i > 0) {
+                    const int k = __builtin_ctz(i);
+                    run += ((r >> k) & 1) ? di[k] : -di[k];
+                }
+                const A2 c = *reinterpret_cast<const A2*>(lut + (run + __builtin_amdgcn_readlane(qi, r)));
+#pragma unroll
+                for (int v = 0; v < NV; v++) {
+                    const Acc xr = vr[v][r], xi = vi[v][r];
+                    vr[v][r] = mul_re(xr, xi, c.x, c.y);
+                    vi[v][r] = mul_im(xr, xi, c.x, c.y);
+                }
+            }
+        } else if (fl & (PT_PHASE_PSI | PT_PHASE_LAM)) {
             // e^{-i gamma E(r)} = e^{-i gamma E(0)} prod_k e^{-i gamma r_k d_k} e^{-i gamma Q(r)};
             // lane r of every wave forms the factor of Q(r), which all lanes then read
             const double2 qf = cis_neg(opa * (es ? ql[1] : ql[0]));

@@ -269,6 +269,11 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
         a.dual_cols = prog.nres;
         a.resident = single ? 1 : 0;
         a.feat = L.nv == 2 ? 1 : feat;
+        if (H && H->qden > 0 && H->scale * H->qden < kTileLut) {
+            // every energy is sum |h| + sum |J| less an even multiple of 1 / q
+            a.lut_n = (int)(H->scale * H->qden) + 1;
+            a.lut_step = 1.0 / H->qden;
+        }
         a.emin = emin;
         a.etol = etol;
         a.amp0 = std::pow(2.0, -0.5 * s->n);

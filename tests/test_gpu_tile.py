@@ -117,3 +117,35 @@ def test_real_couplings_on_the_large_tiles(sv, orc, gam, dtype):
     # the angle itself is known to eps * gamma * sum(|h| + |J|); amplitudes are about 2^-11
     tol = AMP_TOL[dtype] + 2.0 ** -50 * gam * orc.coeff_scale(inst)
     assert np.max(np.abs(s.to_numpy() - ref)) <= tol
+
+
+@pytest.mark.parametrize("dtype,n,total,q", [("c128", 5, 511, 1), ("c128", 5, 512, 1), ("c128", 12, 255.5, 2),
+                                             ("c64", 12, 127.75, 4), ("c64", 14, 511, 1), ("c128", 16, 300, 1)])
+def test_phase_table_edges(sv, dtype, n, total, q):
+    """Grid-valued instances whose phase table is full, one entry too long, and on the finer grids."""
+    rng = np.random.default_rng(n)
+    inst = I.degree4_int2(n, n)
+    h = np.array(inst["h"], dtype=float) / q
+    J = np.array(inst["J"], dtype=float) / q
+    h[0] = 0.0
+    h[0] = total - np.abs(h).sum() - np.abs(J).sum()
+    assert h[0] > 0
+    ei, ej = np.array(inst["ei"]), np.array(inst["ej"])
+    H = sv.Ising(n, h, ei, ej, J)
+    z = np.arange(1 << n)
+    sp = np.where((z[:, None] >> np.arange(n)) & 1, 1.0, -1.0)
+    E = sp @ h + (sp[:, ei] * sp[:, ej]) @ J
+    g, b = rng.uniform(0.1, 1.0, 3), rng.uniform(0.1, 1.0, 3)
+    psi = np.full(1 << n, 2.0 ** (-n / 2), dtype=np.complex128)
+    for gg, bb in zip(g, b):
+        psi *= np.exp(-1j * gg * E)
+        for i in range(n):
+            v = psi.reshape(-1, 2, 1 << i)
+            psi = (np.cos(bb) * v - 1j * np.sin(bb) * v[:, ::-1]).reshape(-1)
+    s = sv.State(n, dtype)
+    e, p, nrm = sv.qaoa_energy(s, H, g, b)
+    tol = 1e-11 if dtype == "c128" else 2e-5
+    want = float((np.abs(psi) ** 2 * E).sum())
+    assert abs(e - want) <= tol * max(1.0, float(np.abs(E).max()))
+    assert abs(nrm - 1.0) <= tol
+    assert np.max(np.abs(s.to_numpy() - psi)) <= tol

@@ -163,6 +163,9 @@ struct GenLayers {
     std::vector<double> m;       // [layer][qubit][8]
     std::vector<uint8_t> unit;   // [layer][qubit]: unit-diagonal form (MIX_GUNIT)
     std::vector<double> mod;     // [layer][qubit]: diagonal modulus of a unit layer, else 1
+    bool folded = false;         // the phase before the last layer applies exp(-i (sum_q th_q s_q + th0))
+    std::vector<double> th;      // [qubit]
+    double th0 = 0.0;
 };
 
 // Tile shapes of a program: [1] one-vector, [2] two-vector.

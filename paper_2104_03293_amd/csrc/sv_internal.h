@@ -66,7 +66,10 @@ enum PointFlags : int32_t {
     PT_SPINZ = 32,      // spin sums: per tile, sum |psi|^2 s_l for every tile bit l and sum |psi|^2
     PT_E2 = 64,         // slot3 += E^2 |psi|^2 (with PT_REDUCE: the spread of E in the state)
     PT_ZETA = 128,      // one-vector passes: psi <- psi (1 + i t E), t = Op::b (after the reductions)
-    PT_EFORM = 256      // one-vector passes: slot2 += E |psi|^2
+    PT_EFORM = 256,     // one-vector passes: slot2 += E |psi|^2
+    PT_DIAG = 512       // passes of complex unit-diagonal layers: the phase of psi also applies exp(-i sum_q th_q s_q); block
+                        // Op::b of PassArgs::gmat: th of tile bit l at l, of qubit q outside the tile at 16 + q,
+                        // a constant angle last
 };
 
 // Per-tile spin partials (PT_SPINZ): kTF columns, column l < T =

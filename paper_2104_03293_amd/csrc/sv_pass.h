@@ -701,6 +701,33 @@ __global__ void __launch_bounds__(1 << (T - R), MINB) k_pass(const PassArgs a) {
                     const SV_CONST double* __restrict__ qph = (const SV_CONST double*)(a.ptab + a.qph_off[op.qidx]);
                     double2 gk[R];
                     double2 run;
+                    // PT_DIAG: the phase also applies a diagonal of single-qubit factors,
+                    // exp(-i sum_q th_q s_q) (two local-field sums more, in one pass of a program)
+                    double th0 = 0.0, thk[R];
+#pragma unroll
+                    for (int k = 0; k < R; k++) thk[k] = 0.0;
+                    if constexpr (GEN == 3) {
+                        if (fl & PT_DIAG) {
+                            const double* __restrict__ D = a.gmat + (size_t)op.b * kGenBlock;
+                            const int q = (int)(t & 63u);
+                            double x = 0.0;
+                            if (q < a.n) x = ((base >> q) & 1ull) ? D[16 + q] : -D[16 + q];
+                            th0 = wave_sum(x) + D[kGenBlock - 1];
+                            uint32_t m = L->tmask;
+#pragma unroll
+                            for (int j = 0; j < T - R; j++) {
+                                const double th = D[__builtin_ctz(m)];
+                                m &= m - 1u;
+                                th0 += ((t >> j) & 1u) ? th : -th;
+                            }
+#pragma unroll
+                            for (int k = 0; k < R; k++) {
+                                thk[k] = D[(L->rbpack >> (4 * k)) & 15u];
+                                th0 -= thk[k];
+                                thk[k] *= 2.0;
+                            }
+                        }
+                    }
                     if (INTE && a.lut_half >= 0) {
                         // energies on the grid Z / q: factors from the table exp(-i gamma m / q)
                         const SV_CONST double* __restrict__ lut =
@@ -722,7 +749,8 @@ __global__ void __launch_bounds__(1 << (T - R), MINB) k_pass(const PassArgs a) {
                         double link = 0.0;
 #pragma unroll
                         for (int k = 0; k < R; k++) {
-                            const double x = fma(0.0, link, 2.0 * gam * f[k]);
+                            const double x = GEN == 3 ? fma(0.0, link, fma(2.0 * gam, f[k], thk[k]))
+                                                      : fma(0.0, link, 2.0 * gam * f[k]);
                             if constexpr (INTE) {
                                 gk[k] = cis_neg(x);
                                 link = gk[k].y;
@@ -733,7 +761,7 @@ __global__ void __launch_bounds__(1 << (T - R), MINB) k_pass(const PassArgs a) {
                                 link = sn;
                             }
                         }
-                        const double x = fma(0.0, link, gam * e0);
+                        const double x = GEN == 3 ? fma(0.0, link, fma(gam, e0, th0)) : fma(0.0, link, gam * e0);
                         if constexpr (INTE) {
                             run = cis_neg(x);
                         } else {

@@ -13,7 +13,7 @@
 // the code is a loop over ops and layouts (one copy of each op's code).
 // Measured against the large tiles: n = 12 complex64, p = 4 (one launch) 93 ->
 // 19 us per evaluation, n = 20 complex64, p = 8 255 -> 114 us, n = 21 real
-// couplings, p = 3 164 -> 86 us, n = 17 gradient, p = 4 436 -> 145 us.  Cycle
+// couplings, p = 3 164 -> 86 us, n = 17 gradient, p = 4 436 -> 138 us.  Cycle
 // stamps of one workgroup (n = 12, double precision in registers): a mixer round
 // 900, a swap of two lane bits 500, an exchange 1500, a phase from the table
 // 2300 (in place 2700), a reduction 2300; start and loads 2100.
@@ -128,8 +128,9 @@ __device__ __forceinline__ void lane_swap(double& a, double& b) {
 // stores see the plain one.  FEAT: 0 uniform mixers, phases and the energy
 // reduction; 1 also the forms of the adjoint sweeps; 2 also general layers and
 // spin sums (each left out where it is not needed: registers and code size).
-template <typename Real, typename Acc, int T, int R, int NV, int FEAT>
-__global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
+// OCC: waves per SIMD the registers are allotted for.
+template <typename Real, typename Acc, int T, int R, int NV, int FEAT, int OCC>
+__global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
     using V2 = typename V2T<Real>::type;
     using A2 = typename V2T<Acc>::type;
     constexpr int NT = 1 << (T - R);
@@ -658,11 +659,21 @@ __global__ void __launch_bounds__(1 << (T - R), 2) k_tile(const TileArgs a) {
 template <typename Real, typename Acc, int NV, int FEAT>
 static int run_tile(int T, const TileArgs& a, hipStream_t st) {
     const dim3 grid(a.dual ? 2u : (unsigned)a.ntiles);
+    // Double-precision variants with forms, general layers or spin sums need 280 registers.  Up to 256
+    // tiles, at most one wave per SIMD runs anyway and may have them (within 256 they spill 44:
+    // gradients n = 10 51.9 -> 45.9 us, n = 17 144 -> 138 us, n = 20 233 -> 211 us, observed runs
+    // n = 17 74.5 -> 69 us); 512 tiles need two waves (n = 21 gradient 325 us, with one 359 us).
+    constexpr int W = FEAT > 0 && sizeof(Acc) == 8 ? 1 : 2;
     switch (T) {
-        case 10: hipLaunchKernelGGL((k_tile<Real, Acc, 10, 4, NV, FEAT>), grid, dim3(64), 0, st, a); break;
-        case 11: hipLaunchKernelGGL((k_tile<Real, Acc, 11, 4, NV, FEAT>), grid, dim3(128), 0, st, a); break;
-        case 12: hipLaunchKernelGGL((k_tile<Real, Acc, 12, 4, NV, FEAT>), grid, dim3(256), 0, st, a); break;
-        case 13: hipLaunchKernelGGL((k_tile<Real, Acc, 13, 4, NV, FEAT>), grid, dim3(512), 0, st, a); break;
+        case 10: hipLaunchKernelGGL((k_tile<Real, Acc, 10, 4, NV, FEAT, W>), grid, dim3(64), 0, st, a); break;
+        case 11: hipLaunchKernelGGL((k_tile<Real, Acc, 11, 4, NV, FEAT, W>), grid, dim3(128), 0, st, a); break;
+        case 12:
+            if (a.ntiles <= 256)
+                hipLaunchKernelGGL((k_tile<Real, Acc, 12, 4, NV, FEAT, W>), grid, dim3(256), 0, st, a);
+            else
+                hipLaunchKernelGGL((k_tile<Real, Acc, 12, 4, NV, FEAT, 2>), grid, dim3(256), 0, st, a);
+            break;
+        case 13: hipLaunchKernelGGL((k_tile<Real, Acc, 13, 4, NV, FEAT, 2>), grid, dim3(512), 0, st, a); break;
         default: return (int)hipErrorInvalidValue;
     }
     return (int)hipGetLastError();

@@ -149,3 +149,18 @@ def test_phase_table_edges(sv, dtype, n, total, q):
     assert abs(e - want) <= tol * max(1.0, float(np.abs(E).max()))
     assert abs(nrm - 1.0) <= tol
     assert np.max(np.abs(s.to_numpy() - psi)) <= tol
+
+
+@pytest.mark.parametrize("n", [20, 21])
+def test_gradients_and_spins_up_to_and_above_256_tiles(sv, n):
+    """Register budgets of the double-precision variants: one wave per SIMD up to 256 tiles, two above."""
+    H = sv.Ising.from_instance(I.degree4_int2(n, n))
+    g, b = I.uniform_params(2, n)
+    s, lam = sv.State(n, "c128"), sv.State(n, "c128")
+    out = []
+    for tile in (-1, 0):
+        with knob(sv, "tile", tile):
+            gr = sv.grad(s, lam, H, g, b)
+            out.append([gr[-2], gr[-1], *sv.aqa_run_observe(s, H, g, b), *sv.qsds_run(s, H, 0.5, g, b, observe=True)])
+    for x, y in zip(*out):
+        assert np.max(np.abs(np.asarray(x) - y)) <= 1e-11 * max(1.0, float(np.max(np.abs(y))))

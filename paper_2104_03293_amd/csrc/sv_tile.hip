@@ -541,21 +541,34 @@ __global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
                 block_sums<1, NW>(gv, s_red, put_at(part2));
             }
         }
+        // Every phase also takes the pending scale, so that it does not pile up over the passes of a
+        // program that runs in one launch (cos(beta) per qubit and mixer: single precision overflows
+        // after some 20 layers of 13 qubits).  The vectors of an adjoint sweep carry the same scale
+        // from PT_LAM_INIT on; a ratio other than 1 goes into lambda.
+        double psc = 1.0;
+        if (fl & (PT_PHASE_PSI | PT_PHASE_LAM)) {
+            psc = pend[0];
+            if constexpr (NV == 2) {
+                const Acc q = (Acc)(pend[1] / psc);
+#pragma unroll
+                for (int r = 0; r < NR; r++) {
+                    vr[1][r] *= q;
+                    vi[1][r] *= q;
+                }
+                pend[1] = 1.0;
+            }
+            pend[0] = 1.0;
+        }
         if ((fl & (PT_PHASE_PSI | PT_PHASE_LAM)) && a.lut_n > 0) {
             // Energies on the grid (2 i - lut_n + 1) / q, 0 <= i < lut_n: the factors of all of them,
             // with the pending scale, in LDS; then one look-up per amplitude (220 instructions per
             // thread and phase instead of 540).
-            double sc = 1.0;
-            if constexpr (NV == 1) {
-                sc = pend[0];
-                pend[0] = 1.0;
-            }
             __syncthreads();  // the look-ups of the phase before
             for (int i = (int)t; i < a.lut_n; i += NT) {
                 const double2 f = cis_neg(opa * ((double)(2 * i - a.lut_n + 1) * a.lut_step));
                 A2 x;
-                x.x = (Acc)(f.x * sc);
-                x.y = (Acc)(f.y * sc);
+                x.x = (Acc)(f.x * psc);
+                x.y = (Acc)(f.y * psc);
                 s_lut[i] = x;
             }
             const double hq = 0.5 / a.lut_step;
@@ -590,11 +603,8 @@ __global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
 #pragma unroll
             for (int k = 0; k < R; k++) gk[k] = cis_neg(opa * d[k]);
             double2 run = cis_neg(opa * e0);
-            if constexpr (NV == 1) {  // long programs: the pending scale does not pile up
-                run.x *= pend[0];
-                run.y *= pend[0];
-                pend[0] = 1.0;
-            }
+            run.x *= psc;
+            run.y *= psc;
 #pragma unroll
             for (int i = 0; i < NR; i++) {
                 const int r = i ^ (i >> 1);

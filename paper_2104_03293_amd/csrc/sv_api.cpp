@@ -298,6 +298,11 @@ static bool tile_angles(const sv_ising_s* H, int p, const double* gamma) {
     return 4.0 * g * H->scale <= kTileMaxAngle;
 }
 
+// Result columns within the range of the small tiles' ops: longer runs take the large tiles, which
+// reduce after every pass.  Per step, a run has its 3 or n + 3 results (one tile) or at most as many
+// columns (T + 1 <= n spin sums of a tile), a gradient layer 2 results and at most 3 columns.
+static bool tile_columns(int steps, int per_step) { return (int64_t)steps * per_step <= kMaxTileColumns; }
+
 extern "C" int sv_init_plus(sv_state s) {
     if (!s) return fail(SV_ERR_ARG, "sv_init_plus: NULL state");
     Plan plan = make_plan(s->n, s->dt);
@@ -447,7 +452,8 @@ extern "C" int sv_aqa_run_observe(sv_state s, sv_ising H, int steps, const doubl
     if (rc) return rc;
     const bool want = pgs_per_step || energy_per_step;
     const bool spins = spinz_per_step != nullptr;
-    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, steps, gamma));
+    Plan plan = make_plan(s->n, s->dt, false, false,
+                          tile_angles(H, steps, gamma) && tile_columns(steps, (want ? 3 : 0) + (spins ? s->n : 0)));
     std::vector<Event> ev;
     forward_events(ev, group_order((int)plan.by_nv[1].size(), (int)s->dt, s->n), steps, gamma, beta, true,
                    want ? 0 : -1);
@@ -632,7 +638,8 @@ extern "C" int sv_qsds_run(sv_state s, sv_ising H, int steps, double tau, const 
     auto add_layer = [&](const double* src) { layers.insert(layers.end(), src, src + (size_t)n * 8); };
     std::vector<double> gam((size_t)steps);
     for (int l = 0; l < steps; l++) gam[l] = tau * B[l];
-    Plan plan = make_plan(n, s->dt, false, true, tile_angles(H, steps, gam.data()));
+    Plan plan = make_plan(n, s->dt, false, true,
+                          tile_angles(H, steps, gam.data()) && tile_columns(steps, (want ? 3 : 0) + (spins ? n : 0)));
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)s->dt, n);
     std::vector<Event> ev;
     if (from_plus) ev.push_back(Event{EV_INIT});
@@ -805,7 +812,7 @@ static int grad_resident(sv_state_s* psi, sv_ising_s* H, int p, const double* ga
 static int grad_zeta(sv_state_s* psi, sv_state_s* lam, sv_ising_s* H, int p, const double* gamma,
                      const double* beta, int psi_is_forward, double* energy, double* p_gs, double* dgamma,
                      double* dbeta) {
-    Plan plan = make_plan(psi->n, psi->dt, false, true, tile_angles(H, p, gamma), false);
+    Plan plan = make_plan(psi->n, psi->dt, false, true, tile_angles(H, p, gamma) && tile_columns(p + 1, 3), false);
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)psi->dt, psi->n);
     const bool fuse = knob_for("fuse", (int)psi->dt, psi->n) != 0;
     const double t = zeta_scale(H);
@@ -877,7 +884,7 @@ extern "C" int sv_grad(sv_state psi, sv_state lam, sv_ising H, int p, const doub
     if ((zeta > 0 || (zeta < 0 && psi->dt == SV_C128)) && zeta_tiles)
         return grad_zeta(psi, lam, H, p, gamma, beta, psi_is_forward, energy, p_gs, dgamma, dbeta);
     // both vectors share one tile geometry: plan with the two-vector shape
-    Plan plan = make_plan(psi->n, psi->dt, true, false, tile_angles(H, p, gamma));
+    Plan plan = make_plan(psi->n, psi->dt, true, false, tile_angles(H, p, gamma) && tile_columns(p + 1, 3));
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)psi->dt, psi->n);
     std::vector<Event> ev;
     if (!psi_is_forward) forward_events(ev, order, p, gamma, beta, true, -1);

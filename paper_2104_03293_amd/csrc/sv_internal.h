@@ -266,6 +266,7 @@ int launch_ground_sets(const GroundSetArgs& a, int nblocks, void* stream);
 // q, q + 1 in lane bits 4 and 5, b | q << 4 = (lbpack >> 8j) & 255.  Reduction columns: part[column][tile].
 constexpr int kTileR = 4;
 constexpr int kMaxTileOps = 104;
+constexpr int kMaxTileColumns = 32767;  // columns, and results, of a program (fields of 15 bits in TileOp::parts)
 // Phase table entries: with 512 of 16 bytes two workgroups of 2^12 complex128 amplitudes still share a CU.
 constexpr int kTileLut = 512;
 constexpr double kTileMaxAngle = 65536.0;  // phase angles gamma * E beyond it use the large tiles

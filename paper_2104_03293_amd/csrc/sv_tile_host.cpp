@@ -190,7 +190,7 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
         }
         if (L.nv == 2 && !lam) return fail(SV_ERR_ARG, "internal: two-vector pass without lam");
     }
-    if (ncol > 32767 || prog.nres * (dual ? 2 : 1) > 32767 || feat == 3)
+    if (ncol > kMaxTileColumns || prog.nres * (dual ? 2 : 1) > kMaxTileColumns || feat == 3)
         return fail(SV_ERR_UNSUPPORTED, "internal: program does not fit the small tiles");
     if (dual && (!single || launches.size() != 1))
         return fail(SV_ERR_UNSUPPORTED, "internal: a paired program needs one launch");

@@ -67,3 +67,43 @@ def test_deep_gradients_of_one_tile_states(sv, orc, n, p, kind, dtype):
                     e, dg, db = sv.grad(psi, lam, H, g, b, psi_is_forward=fwd)
                     assert abs(e - f) <= tol, (zeta, fwd, e, f)
                     assert np.max(np.abs(dg - rg)) <= tol and np.max(np.abs(db - rb)) <= tol, (zeta, fwd)
+
+
+RUN_TOL = {"c128": 1e-10, "c64": 2e-4}  # ten times the parity bars of amplitudes: thousands of layers
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n", [8, 14])
+def test_runs_of_more_steps_than_the_small_tiles_take(sv, orc, n, dtype):
+    """Annealing and Eq. AQA4 runs with more results than the small tiles' ops can name: accepted, and
+    equal to the shorter run of the same steps at every step that both have."""
+    inst = I.degree4_int2(n, n)
+    H = sv.Ising.from_instance(inst)
+    tol = RUN_TOL[dtype] * max(1.0, orc.coeff_scale(inst))
+    s = sv.State(n, dtype)
+    rng = np.random.default_rng(n)
+    for steps, short, observe in ((3000, 1900, True), (11000, 10800, False)):
+        g, b = rng.uniform(0.0, 0.5, steps), rng.uniform(-0.5, 0.5, steps)
+        run = (lambda k: sv.aqa_run_observe(s, H, g[:k], b[:k])) if observe else (
+            lambda k: sv.aqa_run(s, H, g[:k], b[:k], per_step=True))
+        for x, y in zip(run(steps), run(short)):
+            assert x.shape[0] == steps and np.max(np.abs(x[:short] - y)) <= tol
+    g, b = rng.uniform(0.0, 1.0, 3000), rng.uniform(0.0, 1.0, 3000)
+    for x, y in zip(sv.qsds_run(s, H, 0.3, g, b, observe=True), sv.qsds_run(s, H, 0.3, g[:1900], b[:1900], observe=True)):
+        assert np.max(np.abs(x[:1900] - y)) <= tol
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n", [9, 14])
+def test_gradients_of_more_layers_than_the_small_tiles_take(sv, orc, n, dtype):
+    """A circuit followed by thousands of identity layers has the circuit's energy and derivatives."""
+    inst = I.degree4_int2(n, n)
+    H = sv.Ising.from_instance(inst)
+    p = 16400 if n == 9 else 11000
+    g, b = np.zeros(p), np.zeros(p)
+    g[:3], b[:3] = I.uniform_params(3, n)
+    f, rg, rb = orc.grad_tangent(inst, g[:3], b[:3])
+    e, dg, db = sv.grad(sv.State(n, dtype), sv.State(n, dtype), H, g, b)
+    tol = RUN_TOL[dtype] * max(1.0, orc.coeff_scale(inst))
+    assert abs(e - f) <= tol
+    assert np.max(np.abs(dg[:3] - rg)) <= tol and np.max(np.abs(db[:3] - rb)) <= tol

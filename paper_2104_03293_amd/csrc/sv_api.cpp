@@ -290,14 +290,6 @@ static int check_angles(int p, const double* a, const double* b, const char* who
     return SV_OK;
 }
 
-// Phase angles within the range of the small tiles' phase factors (an exponent is at
-// most 4 |gamma| (sum|h| + sum|J|)).
-static bool tile_angles(const sv_ising_s* H, int p, const double* gamma) {
-    double g = 0.0;
-    for (int k = 0; k < p; k++) g = std::max(g, std::fabs(gamma[k]));
-    return 4.0 * g * H->scale <= kTileMaxAngle;
-}
-
 // Result columns within the range of the small tiles' ops: longer runs take the large tiles, which
 // reduce after every pass.  Per step, a run has its 3 or n + 3 results (one tile) or at most as many
 // columns (T + 1 <= n spin sums of a tile), a gradient layer 2 results and at most 3 columns.
@@ -314,7 +306,7 @@ extern "C" int sv_cost_phase(sv_state s, sv_ising H, double gamma) {
     int rc = check_pair(s, H, "sv_cost_phase");
     if (rc) return rc;
     if (!std::isfinite(gamma)) return fail(SV_ERR_NUMERIC, "sv_cost_phase: gamma is not finite");
-    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, 1, &gamma));
+    Plan plan = make_plan(s->n, s->dt);
     Event e{EV_PHASE};
     e.angle = gamma;
     Program prog = build_program({e}, 0, true);
@@ -391,7 +383,7 @@ extern "C" int sv_qaoa_forward(sv_state s, sv_ising H, int p, const double* gamm
     if (rc) return rc;
     rc = check_angles(p, gamma, beta, "sv_qaoa_forward");
     if (rc) return rc;
-    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, p, gamma));
+    Plan plan = make_plan(s->n, s->dt);
     std::vector<Event> ev;
     forward_events(ev, group_order((int)plan.by_nv[1].size(), (int)s->dt, s->n), p, gamma, beta, from_plus != 0, -1);
     Program prog = build_program(ev, 0, knob_for("fuse", (int)s->dt, s->n) != 0);
@@ -421,7 +413,7 @@ int sv_internal_qaoa_energy_fixed(sv_state s, sv_ising H, int p, const double* g
     if (s->device != device)
         return fail(SV_ERR_ARG, "sv_qaoa_energy_noalloc: the state lives on device %d, device %d is current", s->device,
                     device);
-    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, p, gamma));
+    Plan plan = make_plan(s->n, s->dt);
     Program prog = energy_program(s, plan, p, gamma, beta, from_plus);
     return run_program(s, nullptr, H, prog, plan, true, &fx);
 }
@@ -432,7 +424,7 @@ extern "C" int sv_qaoa_energy(sv_state s, sv_ising H, int p, const double* gamma
     if (rc) return rc;
     rc = check_angles(p, gamma, beta, "sv_qaoa_energy");
     if (rc) return rc;
-    Plan plan = make_plan(s->n, s->dt, false, false, tile_angles(H, p, gamma));
+    Plan plan = make_plan(s->n, s->dt);
     Program prog = energy_program(s, plan, p, gamma, beta, from_plus);
     rc = run_program(s, nullptr, H, prog, plan, true);
     if (rc) return rc;
@@ -452,8 +444,10 @@ extern "C" int sv_aqa_run_observe(sv_state s, sv_ising H, int steps, const doubl
     if (rc) return rc;
     const bool want = pgs_per_step || energy_per_step;
     const bool spins = spinz_per_step != nullptr;
+    // (on small tiles, spin sums have no variant for large phase angles)
     Plan plan = make_plan(s->n, s->dt, false, false,
-                          tile_angles(H, steps, gamma) && tile_columns(steps, (want ? 3 : 0) + (spins ? s->n : 0)));
+                          (!spins || small_angles(H, steps, gamma)) &&
+                              tile_columns(steps, (want ? 3 : 0) + (spins ? s->n : 0)));
     std::vector<Event> ev;
     forward_events(ev, group_order((int)plan.by_nv[1].size(), (int)s->dt, s->n), steps, gamma, beta, true,
                    want ? 0 : -1);
@@ -486,6 +480,7 @@ extern "C" int sv_aqa_run_observe(sv_state s, sv_ising H, int steps, const doubl
     }
     Program prog = build_program(live, nres, fuse);
     rc = run_program(s, nullptr, H, prog, plan, want);
+    if (!rc) rc = prepare_tile_passes(s, H, plan);
     if (rc || nres == 0) return rc;
     rc = fetch_results(s, nres);
     if (rc) return rc;
@@ -639,7 +634,7 @@ extern "C" int sv_qsds_run(sv_state s, sv_ising H, int steps, double tau, const 
     std::vector<double> gam((size_t)steps);
     for (int l = 0; l < steps; l++) gam[l] = tau * B[l];
     Plan plan = make_plan(n, s->dt, false, true,
-                          tile_angles(H, steps, gam.data()) && tile_columns(steps, (want ? 3 : 0) + (spins ? n : 0)));
+                          small_angles(H, steps, gam.data()) && tile_columns(steps, (want ? 3 : 0) + (spins ? n : 0)));
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)s->dt, n);
     std::vector<Event> ev;
     if (from_plus) ev.push_back(Event{EV_INIT});
@@ -693,6 +688,7 @@ extern "C" int sv_qsds_run(sv_state s, sv_ising H, int steps, double tau, const 
     prog.nq = n;
     rc = run_program(s, nullptr, H, prog, plan, want);
     if (!rc) rc = prepare_energy_passes(s, H);
+    if (!rc) rc = prepare_tile_passes(s, H, plan);
     if (rc || nres == 0) return rc;
     rc = fetch_results(s, nres);
     if (rc) return rc;
@@ -769,7 +765,7 @@ static double zeta_scale(const sv_ising_s* H) {
 static int grad_resident(sv_state_s* psi, sv_ising_s* H, int p, const double* gamma, const double* beta,
                          int psi_is_forward, double* energy, double* p_gs, double* dgamma, double* dbeta, int* done) {
     *done = 0;
-    Plan plan = make_plan(psi->n, psi->dt, false, false, tile_angles(H, p, gamma));
+    Plan plan = make_plan(psi->n, psi->dt, false, false, small_angles(H, p, gamma));
     if (!plan.tile || plan.by_nv[1].size() != 1) return SV_OK;
     const std::vector<int> order{0};
     std::vector<Event> head;
@@ -812,7 +808,7 @@ static int grad_resident(sv_state_s* psi, sv_ising_s* H, int p, const double* ga
 static int grad_zeta(sv_state_s* psi, sv_state_s* lam, sv_ising_s* H, int p, const double* gamma,
                      const double* beta, int psi_is_forward, double* energy, double* p_gs, double* dgamma,
                      double* dbeta) {
-    Plan plan = make_plan(psi->n, psi->dt, false, true, tile_angles(H, p, gamma) && tile_columns(p + 1, 3), false);
+    Plan plan = make_plan(psi->n, psi->dt, false, true, small_angles(H, p, gamma) && tile_columns(p + 1, 3), false);
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)psi->dt, psi->n);
     const bool fuse = knob_for("fuse", (int)psi->dt, psi->n) != 0;
     const double t = zeta_scale(H);
@@ -844,6 +840,7 @@ static int grad_zeta(sv_state_s* psi, sv_state_s* lam, sv_ising_s* H, int p, con
     rc = fetch_results(lam, 2 * p + 3);
     if (rc) return rc;
     rc = prepare_energy_passes(psi, H);
+    if (!rc) rc = prepare_tile_passes(psi, H, plan);
     if (rc) return rc;
     if (energy) *energy = lam->w.h_res[2 * p + 1];
     if (p_gs) *p_gs = lam->w.h_res[2 * p + 2];
@@ -884,7 +881,7 @@ extern "C" int sv_grad(sv_state psi, sv_state lam, sv_ising H, int p, const doub
     if ((zeta > 0 || (zeta < 0 && psi->dt == SV_C128)) && zeta_tiles)
         return grad_zeta(psi, lam, H, p, gamma, beta, psi_is_forward, energy, p_gs, dgamma, dbeta);
     // both vectors share one tile geometry: plan with the two-vector shape
-    Plan plan = make_plan(psi->n, psi->dt, true, false, tile_angles(H, p, gamma) && tile_columns(p + 1, 3));
+    Plan plan = make_plan(psi->n, psi->dt, true, false, small_angles(H, p, gamma) && tile_columns(p + 1, 3));
     const std::vector<int> order = group_order((int)plan.by_nv[1].size(), (int)psi->dt, psi->n);
     std::vector<Event> ev;
     if (!psi_is_forward) forward_events(ev, order, p, gamma, beta, true, -1);
@@ -932,6 +929,7 @@ extern "C" int sv_grad(sv_state psi, sv_state lam, sv_ising H, int p, const doub
     rc = run_program(psi, lam, H, prog, plan, p_gs != nullptr);
     if (rc) return rc;
     rc = fetch_results(psi, 3 + 2 * p);
+    if (!rc) rc = prepare_tile_passes(psi, H, plan);
     if (rc) return rc;
     if (energy) *energy = psi->w.h_res[1];
     if (p_gs) *p_gs = psi->w.h_res[2];

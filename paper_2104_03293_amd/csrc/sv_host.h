@@ -205,6 +205,8 @@ int gather_results(sv_state_s* s, const double* part, uint64_t ntiles, double* o
 // column, or the norm column (norm) signed by a bit of the tile index.
 void spin_segments(const Geometry& geo, int n, int col, int norm, std::vector<uint32_t>* segs);
 int prepare_passes(sv_state_s* s, sv_ising_s* H, const Program& prog, const Plan& plan);
+bool small_angles(const sv_ising_s* H, int p, const double* gamma);
+int prepare_tile_passes(sv_state_s* s, sv_ising_s* H, const Plan& plan);
 int prepare_tile_pass(sv_ising_s* H, hipStream_t stream, int dt, int T, int group, bool point);
 int drop_results(sv_state_s* s);
 int prepare_energy_passes(sv_state_s* s, sv_ising_s* H);

@@ -269,7 +269,7 @@ constexpr int kMaxTileOps = 104;
 constexpr int kMaxTileColumns = 32767;  // columns, and results, of a program (fields of 15 bits in TileOp::parts)
 // Phase table entries: with 512 of 16 bytes two workgroups of 2^12 complex128 amplitudes still share a CU.
 constexpr int kTileLut = 512;
-constexpr double kTileMaxAngle = 65536.0;  // phase angles gamma * E beyond it use the large tiles
+constexpr double kTileMaxAngle = 65536.0;  // phase angles gamma * E beyond it take the library's sine and cosine
 struct TileOp {
     uint32_t w0;   // OpKind | MixFlags / PointFlags << 8
     uint32_t parts;  // low half: MIX_GBETA, PT_REDUCE: first column; high half: PT_GGAMMA, PT_EFORM: column
@@ -298,7 +298,8 @@ struct TileArgs {
     int32_t dual;           // two workgroups run the program with PT_ZETA's t and -t, the second
     int32_t dual_cols;      //   writing its columns dual_cols further on
     int32_t resident;       // the program runs in one launch of one workgroup
-    int32_t feat;           // kernel variant: 0 plain, 1 adjoint forms, 2 general layers and spin sums
+    int32_t feat;           // kernel variant: 0 plain, 1 adjoint forms, 2 general layers and spin sums, 3 plain with
+                            //   phase angles beyond kTileMaxAngle
     int32_t lut_n;          // energies lie on (2 i - lut_n + 1) lut_step, 0 <= i < lut_n; 0: no phase table
     double lut_step;
     double emin, etol, amp0;

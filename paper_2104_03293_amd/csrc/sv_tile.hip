@@ -127,7 +127,9 @@ __device__ __forceinline__ void lane_swap(double& a, double& b) {
 // exchange leaves from, or arrives in, the swapped form; points, loads and
 // stores see the plain one.  FEAT: 0 uniform mixers, phases and the energy
 // reduction; 1 also the forms of the adjoint sweeps; 2 also general layers and
-// spin sums (each left out where it is not needed: registers and code size).
+// spin sums (each left out where it is not needed: registers and code size);
+// 3 as 0, with the library's sine and cosine for phase angles beyond
+// kTileMaxAngle.
 // OCC: waves per SIMD the registers are allotted for.
 template <typename Real, typename Acc, int T, int R, int NV, int FEAT, int OCC>
 __global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
@@ -147,6 +149,15 @@ __global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
     asm volatile("" ::"s"(a.phantom), "s"(a.nlayouts), "s"(a.lbpack), "s"(a.act), "s"(a.load),
                  "s"(a.store), "s"(a.need_e), "s"(a.nops), "s"(a.dual), "s"(a.lut_n), "s"(a.lut_step), "s"(a.amp0));
     const uint32_t t = threadIdx.x;
+    auto cis = [](double x) {
+        if constexpr (FEAT == 3) {
+            double sn, cs;
+            sincos(x, &sn, &cs);
+            return make_double2(cs, -sn);
+        } else {
+            return cis_neg(x);
+        }
+    };
     // the op list is read where it lies (a dynamic index into a by-value
     // argument would copy it to scratch memory)
     const SV_CONST TileArgs* ka = (const SV_CONST TileArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -565,7 +576,7 @@ __global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
             // thread and phase instead of 540).
             __syncthreads();  // the look-ups of the phase before
             for (int i = (int)t; i < a.lut_n; i += NT) {
-                const double2 f = cis_neg(opa * ((double)(2 * i - a.lut_n + 1) * a.lut_step));
+                const double2 f = cis(opa * ((double)(2 * i - a.lut_n + 1) * a.lut_step));
                 A2 x;
                 x.x = (Acc)(f.x * psc);
                 x.y = (Acc)(f.y * psc);
@@ -598,11 +609,11 @@ __global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
         } else if (fl & (PT_PHASE_PSI | PT_PHASE_LAM)) {
             // e^{-i gamma E(r)} = e^{-i gamma E(0)} prod_k e^{-i gamma r_k d_k} e^{-i gamma Q(r)};
             // lane r of every wave forms the factor of Q(r), which all lanes then read
-            const double2 qf = cis_neg(opa * (es ? ql[1] : ql[0]));
+            const double2 qf = cis(opa * (es ? ql[1] : ql[0]));
             double2 gk[R];
 #pragma unroll
-            for (int k = 0; k < R; k++) gk[k] = cis_neg(opa * d[k]);
-            double2 run = cis_neg(opa * e0);
+            for (int k = 0; k < R; k++) gk[k] = cis(opa * d[k]);
+            double2 run = cis(opa * e0);
             run.x *= psc;
             run.y *= psc;
 #pragma unroll
@@ -692,12 +703,13 @@ static int run_tile(int T, const TileArgs& a, hipStream_t st) {
 template <typename Real, typename Acc>
 static int run_tile_feat(int T, const TileArgs& a, hipStream_t st) {
     if (a.feat == 0) return run_tile<Real, Acc, 1, 0>(T, a, st);
+    if (a.feat == 3) return run_tile<Real, Acc, 1, 3>(T, a, st);
     return a.feat == 1 ? run_tile<Real, Acc, 1, 1>(T, a, st) : run_tile<Real, Acc, 1, 2>(T, a, st);
 }
 
 int launch_tile(int dtype, int nv, int T, const TileArgs& a, void* stream) {
     hipStream_t st = (hipStream_t)stream;
-    if (a.nops < 0 || a.nops > kMaxTileOps || a.nlayouts < 1 || a.nlayouts > kMaxLayouts || a.feat < 0 || a.feat > 2)
+    if (a.nops < 0 || a.nops > kMaxTileOps || a.nlayouts < 1 || a.nlayouts > kMaxLayouts || a.feat < 0 || a.feat > 3)
         return (int)hipErrorInvalidValue;
     if (nv == 2) return dtype == 1 ? run_tile<float, float, 2, 1>(T, a, st) : (int)hipErrorInvalidValue;
     if (dtype == 2) return run_tile_feat<double, double>(T, a, st);

@@ -73,6 +73,32 @@ static void register_couplings(const Geometry& geo, const sv_ising_s* H, int b, 
     }
 }
 
+// Phase angles within the range of the in-place phase factors (an exponent is at most
+// 4 |gamma| (sum|h| + sum|J|)).
+bool small_angles(const sv_ising_s* H, int p, const double* gamma) {
+    double g = 0.0;
+    for (int k = 0; k < p; k++) g = std::max(g, std::fabs(gamma[k]));
+    return 4.0 * g * H->scale <= kTileMaxAngle;
+}
+static bool small_angles(const sv_ising_s* H, const Program& prog) {
+    for (const Pass& p : prog.passes)
+        for (const auto& ph : p.phase)
+            if (!small_angles(H, 1, &ph.second)) return false;
+    return true;
+}
+
+// Calls that may not build tables evaluate energies on the small tiles whatever their angles: a
+// program of the same state that ran on the large tiles instead (angles, or more results than a
+// small-tile program can have) prepares them as one on the small tiles would.
+int prepare_tile_passes(sv_state_s* s, sv_ising_s* H, const Plan& plan) {
+    const int tb = plan.tile ? 0 : tile_bits(s->n, s->dt);
+    for (int grp = 0; tb > 0 && grp < 2; grp++) {
+        int rc = prepare_tile_pass(H, s->stream, (int)s->dt, tb, grp, true);
+        if (rc) return rc;
+    }
+    return SV_OK;
+}
+
 // One launch: a list of ops on the tiles of one group.
 struct TileLaunch {
     int group = 0, nv = 1, load = 1, store = 1;
@@ -192,6 +218,10 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
     }
     if (ncol > kMaxTileColumns || prog.nres * (dual ? 2 : 1) > kMaxTileColumns || feat == 3)
         return fail(SV_ERR_UNSUPPORTED, "internal: program does not fit the small tiles");
+    if (H && !small_angles(H, prog)) {
+        if (feat != 0) return fail(SV_ERR_UNSUPPORTED, "internal: phase angles beyond the small tiles");
+        feat = 3;
+    }
     if (dual && (!single || launches.size() != 1))
         return fail(SV_ERR_UNSUPPORTED, "internal: a paired program needs one launch");
 

@@ -260,6 +260,16 @@ static bool scan_by_spheres(const sv_ising_s* H) {
     return (H->n + 1) * (2.0 * L + 1.0) * 4.0 <= (double)kScanMaxLds;
 }
 
+constexpr int kScanGammas = 1024;  // gammas of one launch at most
+static int64_t scan_coef_blocks(int n_gamma) { return ((int64_t)n_gamma + 3) / 4; }
+
+// Instances of one sphere_scan: the launches over instances (of 256 threads, with scan_coef_blocks,
+// kScanGammas or 32 workgroups for each) hold less than 2^32 threads.
+static size_t scan_instances(int n_gamma) {
+    const int64_t per = std::max<int64_t>({scan_coef_blocks(n_gamma), std::min(n_gamma, kScanGammas), 32});
+    return (size_t)(((int64_t(1) << 24) - 1) / per);
+}
+
 // Scan by sphere sums (sv_scan.hip) of instances idx[].  done[k] = 0 for those with too many
 // ground states, which are left to the direct scan.
 static int sphere_scan(const std::vector<int>& idx, const sv_ising* insts, int n_gamma, const double* gammas,
@@ -288,7 +298,7 @@ static int sphere_scan(const std::vector<int>& idx, const sv_ising* insts, int n
         s.lo = -(int32_t)std::lround(H->qden * H->scale);
         s.zcap = (int32_t)std::min<size_t>(zmax, size_t(1) << H->n);
         s.zoff = ztot;
-        s.out = idx[k];
+        s.out = k;
         xtot += std::max<uint64_t>(8, 1ull << H->n);
         ztot += s.zcap;
         max_n = std::max(max_n, H->n);
@@ -315,7 +325,6 @@ static int sphere_scan(const std::vector<int>& idx, const sv_ising* insts, int n
     if (!ar.alloc()) return fail(SV_ERR_OOM, "sv_batch_p1_scan: device allocation failed");
     std::vector<char> blob(in_bytes);
     memcpy(blob.data() + o_inst, si.data(), ni * sizeof(ScanInst));
-    for (int k = 0; k < ni; k++) reinterpret_cast<ScanInst*>(blob.data() + o_inst)[k].out = k;
     memcpy(blob.data() + o_h, hq.data(), hq.size() * 4);
     if (!cq.empty()) memcpy(blob.data() + o_c, cq.data(), cq.size() * 4);
     memcpy(blob.data() + o_stat, stat.data(), stat.size() * 4);
@@ -338,7 +347,7 @@ static int sphere_scan(const std::vector<int>& idx, const sv_ising* insts, int n
     a.ng = n_gamma;
     a.nb = n_beta;
     a.bpi = (uint32_t)std::min(32, std::max(1, (1 << max_n) / (256 * 8)));
-    a.gpb = (uint32_t)((n_gamma + 3) / 4);
+    a.gpb = (uint32_t)scan_coef_blocks(n_gamma);
     int ke = 0;
     if (e == hipSuccess) ke = launch_scan_tables(a, ni, st);
     if (e == hipSuccess && !ke)
@@ -363,7 +372,7 @@ static int sphere_scan(const std::vector<int>& idx, const sv_ising* insts, int n
     }
     if (uinst.empty()) return SV_OK;
     // sphere sums of a launch: up to 1024 gammas, and as many ground states as fit 64 MiB
-    const int gc = std::min(n_gamma, 1024);
+    const int gc = std::min(n_gamma, kScanGammas);
     const size_t per_unit = (size_t)gc * (kScanMaxN + 1) * sizeof(double2);
     const int64_t units_max =
         std::max<int64_t>(1, std::min<int64_t>((int64_t)uinst.size(), (int64_t)((size_t(64) << 20) / per_unit)));
@@ -441,16 +450,18 @@ extern "C" int sv_batch_p1_scan(int n_inst, const sv_ising* insts, int n_gamma, 
     std::vector<int> grid, rest;
     const bool spheres = knob_for("batchsphere", (int)dtype, 0) != 0;
     for (int i = 0; i < n_inst; i++) (spheres && scan_by_spheres(insts[i]) ? grid : rest).push_back(i);
-    if (!grid.empty()) {
-        std::vector<char> done(grid.size(), 0);
+    const size_t step = scan_instances(n_gamma);
+    for (size_t k0 = 0; k0 < grid.size(); k0 += step) {
+        const std::vector<int> part(grid.begin() + k0, grid.begin() + std::min(k0 + step, grid.size()));
+        std::vector<char> done(part.size(), 0);
         hipEvent_t ev0;
         const bool prof = prof_begin((hipStream_t)stream, &ev0);
-        const int rc = sphere_scan(grid, insts, n_gamma, gammas, n_beta, betas, (hipStream_t)stream, energy_out, pgs_out,
+        const int rc = sphere_scan(part, insts, n_gamma, gammas, n_beta, betas, (hipStream_t)stream, energy_out, pgs_out,
                                    done);
         if (prof) prof_end((hipStream_t)stream, ev0, std::string("batch_") + (dtype == SV_C128 ? "c128" : "c64"), 0.0);
         if (rc) return rc;
-        for (size_t k = 0; k < grid.size(); k++)
-            if (!done[k]) rest.push_back(grid[k]);
+        for (size_t k = 0; k < part.size(); k++)
+            if (!done[k]) rest.push_back(part[k]);
     }
     if (rest.empty()) return SV_OK;
     if ((int)rest.size() == n_inst)

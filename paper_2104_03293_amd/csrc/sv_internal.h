@@ -299,7 +299,7 @@ struct TileArgs {
     int32_t dual_cols;      //   writing its columns dual_cols further on
     int32_t resident;       // the program runs in one launch of one workgroup
     int32_t feat;           // kernel variant: 0 plain, 1 adjoint forms, 2 general layers and spin sums, 3 plain with
-                            //   phase angles beyond kTileMaxAngle
+                            //   phase angles beyond kTileMaxAngle, 4 real general layers only
     int32_t lut_n;          // energies lie on (2 i - lut_n + 1) lut_step, 0 <= i < lut_n; 0: no phase table
     double lut_step;
     double emin, etol, amp0;

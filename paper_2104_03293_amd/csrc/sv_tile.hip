@@ -129,7 +129,11 @@ __device__ __forceinline__ void lane_swap(double& a, double& b) {
 // reduction; 1 also the forms of the adjoint sweeps; 2 also general layers and
 // spin sums (each left out where it is not needed: registers and code size);
 // 3 as 0, with the library's sine and cosine for phase angles beyond
-// kTileMaxAngle.
+// kTileMaxAngle; 4 real general layers and nothing else (twelve Hadamard layers
+// in complex128: n = 13 162 -> 122 us, n = 18 222 -> 186 us, n = 21 312 -> 248 us
+// against the complex form; 127, 191 and 274 us on the large tiles.  Within
+// variant 2 they gave 129, 198 and 275 us, and its double-precision kernels
+// spilled more: complex layers at n = 21 2 % slower).
 // OCC: waves per SIMD the registers are allotted for.
 template <typename Real, typename Acc, int T, int R, int NV, int FEAT, int OCC>
 __global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
@@ -356,6 +360,27 @@ __global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
             // butterflies of register slots K0 .. 3; slot 0 or 2 holds tile bit p0 or p2
             auto round = [&](auto k0, uint32_t act, int p0, int p2) {
                 constexpr int K0 = decltype(k0)::value;
+                if (FEAT == 4) {
+                    // real matrices: half the arithmetic of the general form
+                    const SV_CONST double* M = (const SV_CONST double*)(a.gmat + (uint64_t)aux * kGenBlock);
+#pragma unroll
+                    for (int k = K0; k < R; k++) {
+                        if (!((act >> k) & 1)) continue;
+                        const SV_CONST double* m = M + 8 * (k < 2 ? p0 + k : p2 + k - 2);
+                        const Acc a0 = (Acc)m[0], b0 = (Acc)m[2], c0 = (Acc)m[4], d0 = (Acc)m[6];
+#pragma unroll
+                        for (int r = 0; r < NR; r++) {
+                            if (r & (1 << k)) continue;
+                            const int r2 = r | (1 << k);
+                            const Acc ur = vr[0][r], ui = vi[0][r], wr = vr[0][r2], wi = vi[0][r2];
+                            vr[0][r] = fma(a0, ur, b0 * wr);
+                            vi[0][r] = fma(a0, ui, b0 * wi);
+                            vr[0][r2] = fma(c0, ur, d0 * wr);
+                            vi[0][r2] = fma(c0, ui, d0 * wi);
+                        }
+                    }
+                    return;
+                }
                 if (FEAT == 2 && (fl & MIX_GEN)) {
                     // general single-qubit layer: (u, v) <- (m00 u + m01 v, m10 u + m11 v)
                     const SV_CONST double* M = (const SV_CONST double*)(a.gmat + (uint64_t)aux * kGenBlock);
@@ -455,6 +480,7 @@ __global__ void __launch_bounds__(1 << (T - R), OCC) k_tile(const TileArgs a) {
             }
             continue;
         }
+        if constexpr (FEAT == 4) continue;
         // ---- OP_POINT in the current layout (0 or K - 1)
         const int es = cur == 0 ? 0 : 1;
         double e0 = es ? ev[1][0] : ev[0][0], d[R];
@@ -704,12 +730,13 @@ template <typename Real, typename Acc>
 static int run_tile_feat(int T, const TileArgs& a, hipStream_t st) {
     if (a.feat == 0) return run_tile<Real, Acc, 1, 0>(T, a, st);
     if (a.feat == 3) return run_tile<Real, Acc, 1, 3>(T, a, st);
+    if (a.feat == 4) return run_tile<Real, Acc, 1, 4>(T, a, st);
     return a.feat == 1 ? run_tile<Real, Acc, 1, 1>(T, a, st) : run_tile<Real, Acc, 1, 2>(T, a, st);
 }
 
 int launch_tile(int dtype, int nv, int T, const TileArgs& a, void* stream) {
     hipStream_t st = (hipStream_t)stream;
-    if (a.nops < 0 || a.nops > kMaxTileOps || a.nlayouts < 1 || a.nlayouts > kMaxLayouts || a.feat < 0 || a.feat > 3)
+    if (a.nops < 0 || a.nops > kMaxTileOps || a.nlayouts < 1 || a.nlayouts > kMaxLayouts || a.feat < 0 || a.feat > 4)
         return (int)hipErrorInvalidValue;
     if (nv == 2) return dtype == 1 ? run_tile<float, float, 2, 1>(T, a, st) : (int)hipErrorInvalidValue;
     if (dtype == 2) return run_tile_feat<double, double>(T, a, st);

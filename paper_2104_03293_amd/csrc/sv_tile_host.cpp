@@ -104,6 +104,7 @@ struct TileLaunch {
     int group = 0, nv = 1, load = 1, store = 1;
     std::vector<TileOp> ops;
     std::vector<int> layer;  // per op: general layer index or -1
+    bool real = false;       // its ops are general layers with real matrices
 };
 
 int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, const Plan& plan, bool need_ground,
@@ -255,17 +256,23 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
         double* h = nullptr;
         int rc = stage_matrices(s, (size_t)nblk, &h);
         if (rc) return rc;
-        for (const TileLaunch& L : launches)
+        for (TileLaunch& L : launches) {
+            L.real = L.nv == 1 && !L.ops.empty();
             for (size_t i = 0; i < L.ops.size(); i++) {
-                if (L.layer[i] < 0) continue;
+                if (L.layer[i] < 0) {
+                    L.real = false;
+                    continue;
+                }
                 const Geometry& geo = groups[L.group];
                 double* blk = h + (size_t)L.ops[i].aux * kGenBlock;
                 for (int l = 0; l < kGenBlock / 8; l++) {
                     const int q = l < T && l < s->n ? (l < geo.c ? l : geo.lo + (l - geo.c)) : -1;
                     const double id[8] = {1, 0, 0, 0, 0, 0, 1, 0};
                     memcpy(blk + 8 * l, q < 0 ? id : prog.layers + ((size_t)L.layer[i] * s->n + q) * 8, 8 * sizeof(double));
+                    for (int x = 1; x < 8; x += 2) L.real = L.real && blk[8 * l + x] == 0.0;
                 }
             }
+        }
         rc = send_matrices(s, (size_t)nblk);
         if (rc) return rc;
     }
@@ -298,7 +305,7 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
         a.dual = dual ? 1 : 0;
         a.dual_cols = prog.nres;
         a.resident = single ? 1 : 0;
-        a.feat = L.nv == 2 ? 1 : feat;
+        a.feat = L.nv == 2 ? 1 : L.real ? 4 : feat;
         if (H && H->qden > 0 && H->scale * H->qden < kTileLut) {
             // every energy is sum |h| + sum |J| less an even multiple of 1 / q
             a.lut_n = (int)(H->scale * H->qden) + 1;

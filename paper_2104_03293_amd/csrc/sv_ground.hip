@@ -1,5 +1,5 @@
-// Ground states of instances on an energy grid by enumeration over an
-// independent set: k spins without couplings among each other are, given the
+// Ground states: of small states from their energy table (k_ground_table), of
+// instances on an energy grid by enumeration over an independent set: k spins without couplings among each other are, given the
 // other r = n - k, each at its own best value, so
 //   min_z E(z) = min_x ( E_rest(x) - sum_i |F_i(x)| ),   F_i = h_i + sum_j J_ij s_j(x),
 // over the 2^r settings x of the rest; a setting at the minimum stands for
@@ -133,6 +133,51 @@ __global__ void __launch_bounds__(256) k_ground_sets_finish(const GroundSetArgs 
         a.out[1] = best.cnt;
         a.out[2] = best.first;
     }
+}
+
+// Small states: minimum, number of states at it (within tol) and the first of them from the energy
+// table that the small tiles read, one workgroup.  Bound by its latency (16 loads in series with two
+// reductions, in the shadow of the call's allocations and copy).
+__global__ void __launch_bounds__(1024) k_ground_table(const double* __restrict__ E, uint32_t N, double tol, double* out) {
+    __shared__ double s_m[16];
+    __shared__ uint32_t s_c[16], s_f[16];
+    const uint32_t t = threadIdx.x;
+    double m = INFINITY;
+    for (uint32_t z = t; z < N; z += 1024) m = fmin(m, E[z]);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) m = fmin(m, __shfl_xor(m, off));
+    if ((t & 63) == 0) s_m[t >> 6] = m;
+    __syncthreads();
+    for (int w = 0; w < 16; w++) m = fmin(m, s_m[w]);
+    uint32_t cnt = 0, first = 0xffffffffu;
+    for (uint32_t z = t; z < N; z += 1024)
+        if (fabs(E[z] - m) <= tol) {
+            cnt++;
+            first = min(first, z);
+        }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        cnt += __shfl_xor(cnt, off);
+        first = min(first, (uint32_t)__shfl_xor(first, off));
+    }
+    if ((t & 63) == 0) {
+        s_c[t >> 6] = cnt;
+        s_f[t >> 6] = first;
+    }
+    __syncthreads();
+    if (t != 0) return;
+    for (int w = 1; w < 16; w++) {
+        cnt += s_c[w];
+        first = min(first, s_f[w]);
+    }
+    out[0] = m;
+    out[1] = (double)cnt;
+    out[2] = (double)first;
+}
+
+int launch_ground_table(const double* E, int n, double tol, double* out, void* stream) {
+    hipLaunchKernelGGL(k_ground_table, dim3(1), dim3(1024), 0, (hipStream_t)stream, E, 1u << n, tol, out);
+    return (int)hipGetLastError();
 }
 
 int launch_ground_sets(const GroundSetArgs& a, int nblocks, void* stream) {

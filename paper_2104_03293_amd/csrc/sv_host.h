@@ -207,6 +207,8 @@ void spin_segments(const Geometry& geo, int n, int col, int norm, std::vector<ui
 int prepare_passes(sv_state_s* s, sv_ising_s* H, const Program& prog, const Plan& plan);
 bool small_angles(const sv_ising_s* H, int p, const double* gamma);
 int prepare_tile_passes(sv_state_s* s, sv_ising_s* H, const Plan& plan);
+// Ground states of an instance of at most 14 qubits whose states run on small tiles of T bits.
+int run_ground_table(sv_ising_s* H, hipStream_t stream, int T);
 int prepare_tile_pass(sv_ising_s* H, hipStream_t stream, int dt, int T, int group, bool point);
 int drop_results(sv_state_s* s);
 int prepare_energy_passes(sv_state_s* s, sv_ising_s* H);

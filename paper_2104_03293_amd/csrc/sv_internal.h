@@ -259,6 +259,8 @@ struct GroundSetArgs {
     unsigned long long* out;     // energy, count, first index
 };
 int launch_ground_sets(const GroundSetArgs& a, int nblocks, void* stream);
+// out: minimum, number of states within tol of it, first of them (n <= 31)
+int launch_ground_table(const double* E, int n, double tol, double* out, void* stream);
 
 // ---------------------------------------------------------------- small tiles
 // Tile programs of states that the large tiles cannot spread over the chip

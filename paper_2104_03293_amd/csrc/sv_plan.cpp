@@ -1504,18 +1504,10 @@ int run_ground(sv_ising_s* H, hipStream_t stream) {
         if (H->has_ground) return SV_OK;
     }
     const sv_dtype dt = SV_C64;  // enumeration tiles use the complex64 tile shape
-    if (const int tb = tile_bits(H->n, dt); tb > 0 && H->n <= 14) {
-        // complex64 energy evaluations of up to 14 qubits need no table beyond this one: those that
-        // may not build any (tile_seen) follow sv_ground alone
-        for (int grp = 0; grp < 2; grp++) {
-            int rc = prepare_tile_pass(H, stream, (int)dt, tb, grp, true);
-            if (rc) return rc;
-        }
-    }
+    if (const int tb = tile_bits(H->n, dt); tb > 0 && H->n <= 14) return run_ground_table(H, stream, tb);
     int done = 0;
     int rc = run_ground_sets(H, stream, &done);
     if (rc || done) return rc;
-    const Shape sh = shape_for((int)dt, 1, false);
     std::vector<Geometry> groups = plan_groups(H->n, dt, 1);
     const Geometry& geo = groups[0];
     GeoBuf* gb = nullptr;
@@ -1524,7 +1516,6 @@ int run_ground(sv_ising_s* H, hipStream_t stream) {
     const double* tf = nullptr;
     rc = get_tf(H, geo, gb, stream, &tf);
     if (rc) return rc;
-    (void)sh;
     double* d_e = nullptr;
     uint64_t *d_c = nullptr, *d_a = nullptr;
     double* d_out = nullptr;

@@ -53,3 +53,36 @@ def test_ground_by_sets_matches_tile_enumeration(sv, n):
     e, deg, arg = sv.ground(sv.Ising.from_instance(inst))
     e3, deg3, arg3 = sv.ground(sv.Ising.from_instance(scaled(inst, 1.0 / 3.0)))
     assert (deg, arg) == (deg3, arg3) and abs(e / 3.0 - e3) <= 1e-9 * abs(e)
+
+
+SMALL = [("int", lambda n: I.fields_only(n, n) if n < 5 else I.make_instance(
+             n, I.gnm_edges(n, min(2 * n, n * (n - 1) // 2), np.random.default_rng(n)),
+             np.random.default_rng(n + 1).integers(-1, 2, n), np.ones(min(2 * n, n * (n - 1) // 2)))),
+         ("real", lambda n: I.random_real(n, n * (n - 1) // 2, n) if n > 1 else I.fields_only(1, 2)),
+         ("zero", lambda n: I.make_instance(n, np.zeros((0, 2)), np.zeros(n), np.zeros(0)))]
+
+
+@pytest.mark.parametrize("kind,make", SMALL, ids=[c[0] for c in SMALL])
+@pytest.mark.parametrize("n", [1, 2, 5, 6, 9, 10, 11, 13, 14, 15])
+def test_ground_of_small_states_from_the_energy_table(sv, orc, n, kind, make):
+    """Up to 14 qubits the states are counted in the energy table (15: not), and a complex64 evaluation
+    that may not build tables follows sv_ground alone, complex128 ones do not."""
+    import torch
+
+    inst = make(n)
+    H = sv.Ising.from_instance(inst)
+    e, deg, arg = sv.ground(H)
+    E = orc.energies(inst)
+    at = np.flatnonzero(np.abs(E - E.min()) <= orc.ground_tol(inst))
+    assert (deg, arg) == (len(at), at[0]) and abs(e - E.min()) <= 1e-14 * max(1.0, orc.coeff_scale(inst))
+    out = torch.zeros(3, dtype=torch.float64, device="cuda")
+    for dtype in ("c128", "c64"):
+        s = sv.State(n, dtype)
+        if dtype == "c64" and n <= 14:
+            sv.qaoa_energy_noalloc(s, H, [0.3], [0.2], out)
+            e2, p2, n2 = sv.qaoa_energy(s, H, [0.3], [0.2])
+            assert out.cpu().tolist() == [n2, e2, p2]
+        else:
+            with pytest.raises(sv.SVError) as err:
+                sv.qaoa_energy_noalloc(s, H, [0.3], [0.2], out)
+            assert err.value.code == 4

@@ -24,9 +24,15 @@
  *     sv_last_error() returns a thread-local message.  Argument errors leave
  *     every object unchanged.  After a HIP error a state is marked failed and
  *     later calls on it return SV_ERR_HIP.
- *   - Calls that return host scalars (sv_expect, sv_grad, sv_ground,
- *     sv_aqa_run with outputs, sv_batch_p1_scan) synchronise the state's
- *     stream before returning; all other calls only enqueue work.
+ *   - Calls that return host scalars (sv_expect, sv_qaoa_energy, sv_grad,
+ *     sv_spin_z, sv_ground, sv_aqa_run and sv_qsds_run with outputs,
+ *     sv_batch_p1_scan) synchronise: they return once all work enqueued before
+ *     them on the state's stream and their own kernels have done everything
+ *     that can be seen, so the results are there and the state may be read,
+ *     freed or used on any stream.  Short programs learn this from their
+ *     results, which the last kernel writes to host memory, instead of from
+ *     the stream: hipStreamQuery may report that kernel as still running for
+ *     some microseconds after the call.  All other calls only enqueue work.
  *   - Objects are not thread-safe: calls that use one state or instance from
  *     several host threads at once must be serialised by the caller.
  */

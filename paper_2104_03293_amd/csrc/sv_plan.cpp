@@ -265,15 +265,16 @@ std::vector<Geometry> plan_groups(int n, sv_dtype dt, int nv, bool grad, bool ge
 // knob that is not at its default asks for plan_groups' plans.
 bool two_group_tiles(int n, sv_dtype dt, bool base_tiles, int* T) {
     if (knob_for("twogroup", (int)dt, n) == 0 || knob_for("split", (int)dt, n) != 0) return false;
-    if (dt == SV_C128) {
-        if (knob_for("cmin128", (int)dt, n) != 3 || knob_for("c128t14", (int)dt, n) != 0) return false;
-        *T = n == 24 ? 13 : 14;
-        return n == 24 || (!base_tiles && (n == 25 || n == 26));
-    }
-    if (knob_for("cmin64", (int)dt, n) != 4 || knob_for("c64occ", (int)dt, n) != 1 || knob_for("c64t13", (int)dt, n) != 0)
+    const bool c128 = dt == SV_C128;
+    if (c128 ? knob_for("cmin128", (int)dt, n) != 3 || knob_for("c128t14", (int)dt, n) != 0
+             : knob_for("cmin64", (int)dt, n) != 4 || knob_for("c64occ", (int)dt, n) != 1 || knob_for("c64t13", (int)dt, n) != 0)
         return false;
-    *T = 14;
-    return n == 25;
+    // two groups of T-bit tiles hold T + (T - c) qubits with runs of 2^c amplitudes in the strided one
+    const int base = shape_for((int)dt, 1, false).T, c64B = c128 ? 2 : 3, top = base_tiles ? base : 14;
+    if (n <= 2 * base - (c64B + 1)) return false;  // plan_groups has two with runs of 128 bytes
+    for (*T = base; *T <= top; ++*T)
+        if (n <= 2 * *T - c64B) return true;
+    return false;
 }
 
 std::vector<Geometry> two_groups(int n, sv_dtype dt, int T) {
@@ -1213,9 +1214,11 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
         a.nslots = (int)p.slot_dst.size();
         a.nops = 0;
         a.need_e = 0;
-        // (states of 128 and 256 MiB stay in the last-level cache between passes: plain accesses are
-        // 2-9 % faster there, n = 24 complex128 1257 -> 1200 us, and 6 % slower at 64 MiB)
-        const bool cached = s->bytes > (size_t(64) << 20) && s->bytes <= (size_t(256) << 20);
+        // States up to the size of the last-level cache stay in it between passes: plain accesses are
+        // 2-9 % faster there (256 MiB, n = 24 complex128 1257 -> 1200 us; 128 MiB 2 %), but 6 % slower
+        // at a quarter of it, and 9 % above it.
+        constexpr size_t kLastLevelCache = size_t(256) << 20;
+        const bool cached = s->bytes > kLastLevelCache / 4 && s->bytes <= kLastLevelCache;
         a.nt = (geo.phantom == 0 && geo.c >= ntmin && !cached) ? 3 : 0;
         if (geo.phantom == 0 && !cached && (p.load & 4) && knob_for("ntinit", (int)s->dt, s->n) != 0) a.nt = 3;
         a.swz = lds_swz_bits(s->dt, s->n);
@@ -1383,11 +1386,17 @@ int drop_results(sv_state_s* s) {
     return SV_OK;
 }
 
+static inline void spin_wait() {
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#endif
+}
+
 // Results that the last kernel of a program writes to pinned memory are read as they arrive: the
 // kernels before it, and with them the state, are complete by then, and waiting for the stream
 // takes 3-15 us longer (per energy: n = 14 complex128 p = 1 29.7 -> 26.8 us, n = 20 complex64 p = 8
-// 132 -> 117 us; an observed run of 0.6 ms 620 -> 577 us).  Long programs, and results that do not arrive (a failed
-// kernel, a NaN with the mark's payload), wait for the stream.
+// 132 -> 117 us; an observed run of 0.6 ms 620 -> 577 us).  Long programs, and results that do not
+// arrive (a failed kernel, a NaN with the mark's payload), wait for the stream.
 int fetch_results(sv_state_s* s, int nres) {
     if (nres <= 0) return SV_OK;
     if (s->w.res_on_host && s->w.awaited == nres) {
@@ -1400,7 +1409,7 @@ int fetch_results(sv_state_s* s, int nres) {
             else if ((spin & 63) == 63 && std::chrono::steady_clock::now() > end)
                 break;
             else
-                __builtin_ia32_pause();
+                spin_wait();
         }
         std::atomic_thread_fence(std::memory_order_acquire);
         if (i == nres) {

@@ -23,9 +23,9 @@
 // The direct scan (k_batch_* in sv_kernels.hip) mixes 2^n amplitudes for every
 // grid point; it remains for instances off the grid, and for those with more
 // ground states than grid points, where the histograms would cost more.
-// 128 instances of 10 to 18 qubits on a 32 x 32 grid: 29.7 -> 0.79 ms a call, of which 0.17 ms are
-// kernels (bound by the index pass and the LDS atomics of the histograms) and the rest copies of
-// the results, allocations and the two waits for the host.
+// 128 instances of 10 to 18 qubits on a 32 x 32 grid: 29.7 -> 0.53 ms a call (0.9-1.1 ms where every
+// call brings new instances), of which 0.17 ms are kernels (bound by the index pass and the LDS atomics
+// of the histograms) and the rest copies of the results, allocations and the two waits for the host.
 #include <hip/hip_runtime.h>
 
 #include "sv_device.h"

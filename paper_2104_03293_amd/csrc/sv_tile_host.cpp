@@ -272,8 +272,8 @@ int run_tile_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& pro
         int rc = ensure_work(s, part_need, std::max(nres, 1));
         if (rc) return rc;
         part = s->w.d_part;
-        // the last stage writes the results to the pinned host buffer (every call that asks for
-        // results waits for the stream before it reads them)
+        // the last stage writes the results to the pinned host buffer, from which fetch_results reads
+        // them as they arrive (gather_results) or after the stream (one tile)
         out = s->w.h_res;
         s->w.res_on_host = true;
     }

@@ -765,8 +765,9 @@ static double zeta_scale(const sv_ising_s* H) {
 static int grad_resident(sv_state_s* psi, sv_ising_s* H, int p, const double* gamma, const double* beta,
                          int psi_is_forward, double* energy, double* p_gs, double* dgamma, double* dbeta, int* done) {
     *done = 0;
-    Plan plan = make_plan(psi->n, psi->dt, false, false, small_angles(H, p, gamma));
-    if (!plan.tile || plan.by_nv[1].size() != 1) return SV_OK;
+    // (before planning: the plan of a larger state takes 20-60 us of host time)
+    if (psi->n > tile_bits(psi->n, psi->dt) || !small_angles(H, p, gamma)) return SV_OK;
+    Plan plan = make_plan(psi->n, psi->dt);
     const std::vector<int> order{0};
     std::vector<Event> head;
     if (!psi_is_forward) forward_events(head, order, p, gamma, beta, true, -1);
@@ -834,13 +835,14 @@ static int grad_zeta(sv_state_s* psi, sv_state_s* lam, sv_ising_s* H, int p, con
     if (rc) return rc;
     rc = run_program(psi, nullptr, H, minus, plan, false);
     if (rc) return rc;
+    // while the programs run
+    rc = prepare_energy_passes(psi, H);
+    if (!rc) rc = prepare_tile_passes(psi, H, plan);
+    if (rc) return rc;
     // psi's results come last on the stream both programs ran on
     rc = fetch_results(psi, 2 * p);
     if (rc) return rc;
     rc = fetch_results(lam, 2 * p + 3);
-    if (rc) return rc;
-    rc = prepare_energy_passes(psi, H);
-    if (!rc) rc = prepare_tile_passes(psi, H, plan);
     if (rc) return rc;
     if (energy) *energy = lam->w.h_res[2 * p + 1];
     if (p_gs) *p_gs = lam->w.h_res[2 * p + 2];

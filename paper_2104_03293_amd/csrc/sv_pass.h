@@ -861,6 +861,10 @@ static void launch_gen_fast(const PassArgs& a, dim3 grid, dim3 block, hipStream_
     // three or more layouts with complex matrices on complex128 amplitudes need the whole
     // register file (one workgroup per CU)
     constexpr int MB = (sizeof(Real) == 8 && GC == 1) ? 1 : GMB;
+    // complex64 unit layers with two layouts: held to the 128 registers of two workgroups per CU, which
+    // they exceed by two (spilled) since their phase may apply single-qubit diagonals (PT_DIAG); ten
+    // Eq. AQA4 steps, n = 27: 14.1 -> 11.6 ms
+    constexpr int MB2 = (sizeof(Real) == 4 && GC == 3) ? 4 : GMB;
     if (a.nlayouts == 1) {
         if (rm) hipLaunchKernelGGL((k_pass<Real, T, R, 1, NS, GMB, false, true, 1, NTM, false, false, GR>), grid, block,
                                    0, st, a);
@@ -869,7 +873,7 @@ static void launch_gen_fast(const PassArgs& a, dim3 grid, dim3 block, hipStream_
     } else if (a.nlayouts == 2) {
         if (rm) hipLaunchKernelGGL((k_pass<Real, T, R, 1, NS, GMB, false, true, 2, NTM, false, false, GR>), grid, block,
                                    0, st, a);
-        else hipLaunchKernelGGL((k_pass<Real, T, R, 1, NS, GMB, false, true, 2, NTM, false, false, GC>), grid, block, 0,
+        else hipLaunchKernelGGL((k_pass<Real, T, R, 1, NS, MB2, false, true, 2, NTM, false, false, GC>), grid, block, 0,
                                 st, a);
     } else if (a.kc34 && a.nlayouts == 3) {  // straight-line walk
         if (rm) hipLaunchKernelGGL((k_pass<Real, T, R, 1, NS, GMB, false, true, 3, NTM, false, false, GR>), grid, block,

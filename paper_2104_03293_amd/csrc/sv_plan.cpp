@@ -1287,7 +1287,8 @@ int run_program(sv_state_s* s, sv_state_s* lam, sv_ising_s* H, Program& prog, co
             if (p.ops[i].flags & MIX_GUNIT) a.gen_unit = 1;  // every general op of the pass, by construction
         }
         for (const Op& op : p.ops)
-            if (op.kind == OP_POINT && (op.flags & PT_DIAG)) a.gen_real = 0;
+            // (the kernels of real layers take phases on the energy grid only)
+            if (op.kind == OP_POINT && ((op.flags & PT_DIAG) || (!p.phase.empty() && lut_half < 0))) a.gen_real = 0;
         hipEvent_t ev0;
         const bool prof = !fx && prof_begin(s->stream, &ev0);
         int e = take_injected_failure() ? (int)hipErrorLaunchFailure : launch_pass((int)s->dt, p.nv, geo.T, geo.R, a, s->stream);

@@ -6,6 +6,8 @@ import sys
 import numpy as np
 import pytest
 
+from paper_2104_03293_amd import inputs as I
+
 pytestmark = pytest.mark.gpu
 AMP_TOL = {"c128": 1e-11, "c64": 2e-5}  # parity bars of the whole library
 
@@ -42,3 +44,25 @@ def test_real_and_mixed_layers(sv, orc, n, layers, mixed, dtype):
     s.from_numpy(psi)
     sv.gate_layers(s, U)
     assert np.max(np.abs(s.to_numpy() - orc.gate_layers(n, psi, U))) <= AMP_TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("tile", [-1, 0])
+@pytest.mark.parametrize("n,kind", [(15, "real"), (16, "int"), (22, "real")])
+def test_real_layers_beside_phases(sv, orc, n, kind, tile, dtype):
+    """Eq. AQA4 steps without fields have identity layers, real ones, beside the phases of couplings on
+    and off the energy grid; with an x field in some steps, complex ones in other passes."""
+    inst = I.random_real(n, 2 * n, n) if kind == "real" else I.degree4_int2(n, n)
+    inst = I.make_instance(n, np.stack([inst["ei"], inst["ej"]], 1), np.zeros(n), inst["J"])
+    H = sv.Ising.from_instance(inst)
+    s = sv.State(n, dtype)
+    old = sv.tune_get("tile")
+    sv.tune_set("tile", tile)
+    try:
+        for A in ([0.0, 0.0, 0.0], [0.0, 0.9, 0.0], [0.7, 0.0, 0.0]):
+            B = [0.3, 1.0, 0.6]
+            sv.qsds_run(s, H, 0.8, A, B)
+            psi = orc.qsds_run(inst, 0.8, A, B)
+            assert np.max(np.abs(s.to_numpy() - psi)) <= AMP_TOL[dtype]
+    finally:
+        sv.tune_set("tile", old)
